@@ -425,8 +425,8 @@ __global__ __launch_bounds__(256) void k_finish_loop(Ctrl* ctrl, Hist* hist,
   if (threadIdx.x == 0) {
     const int n = max_iter;
     const double e = fabs(t1 - t2);
-    const bool stop = stop_test(t1, e, n, hist->err, n_occ, tol, stop_rule, stall_gate,
-                                ctrl->stall_from);
+    const bool stop = stop_test(t1, e, n, err_before(hist->err, n), n_occ, tol, stop_rule,
+                                stall_gate, ctrl->stall_from);
     hist->t1[n] = t1;
     hist->t2[n] = t2;
     hist->err[n] = e;

@@ -21,6 +21,7 @@
 #include "sp2_gemm.hpp"
 #include "sp2_lanczos.hpp"
 #include "sp2_nvt.hpp"
+#include "sp2_wave.hpp"
 #include "sp2_xl.hpp"
 
 using namespace sp2;
@@ -72,6 +73,7 @@ constexpr int64_t kChunkLargeNp = 4096;
 constexpr int kInitBlocksMax = 1024;   // partial pairs written by the input layer
 constexpr size_t kPartialBytes = size_t(64) << 20;   // split-K tail accumulators
 constexpr int kMaxTailTiles = 1024;                   // split-K tail tiles per launch
+constexpr size_t kPieceBytes = size_t(256) * 4 * 4 * 16 * 4;   // one 256x256 FP32 accumulator
 
 int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 
@@ -389,9 +391,8 @@ int wgs_per_cu(K kernel, int threads) {
 // given layout and device).
 template <int KIND>
 Decomp split_decomp(const WS& w) {
-  constexpr size_t piece = size_t(256) * 4 * 4 * 16 * 4;   // one 256x256 FP32 accumulator
   const int slots = device_cus() * wgs_per_cu(k_sym_split<KIND>, 256);
-  return plan_decomp(w, static_cast<int>(w.L.np / 256), slots, static_cast<int>(w.L.np / 32), piece);
+  return plan_decomp(w, static_cast<int>(w.L.np / 256), slots, static_cast<int>(w.L.np / 32), kPieceBytes);
 }
 
 Decomp split_decomp_of(const WS& w, int precision) {
@@ -401,12 +402,68 @@ Decomp split_decomp_of(const WS& w, int precision) {
   return split_decomp<kFP16X3>(w);
 }
 
+// Tile rows (32 or 64) of the k_sym_wave launches of this order, 0 where they
+// run on the 256 x 256 kernel: a launch of few tiles is bound by its latency,
+// so 32 rows while they make one round of the machine, 64 while they make two.
+// us per FP16X3 layer, 32-row tiles / 64-row / 256 x 256 kernel: n = 402 8.6 /
+// 11.2 / 25.8; n = 750 16.3 / 13.7 / 31; n = 1026 24 / 17.7 / 35.6; n = 1536 - /
+// 33 / 46; n = 1980 - / 43.8 / 59; n = 2046 (three rounds) - / 55 / 60.
+// It depends on the order alone: a launch over n rows leaves padding unwritten
+// that the 256 x 256 kernel would read.
+int wave_rows(const Layout& L) {
+  const int cus = device_cus();
+  const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64;
+  if (a * (a + 1) / 2 <= std::min(cus, L.max_parts)) return 32;
+  if (b * (b + 1) / 2 <= std::min(2 * cus, L.max_parts)) return 64;
+  return 0;
+}
+
+// Wave launch covering the first `cover` rows, nseg K segments.
+WaveGrid wave_grid(const WS& w, int64_t cover, int nseg) {
+  const Layout& L = w.L;
+  WaveGrid g;
+  const int T = wave_rows(L);
+  g.lim = static_cast<int>(round_up(L.n, 64));
+  g.nt = static_cast<int>((std::max<int64_t>(cover, g.lim) + T - 1) / T);
+  g.ntiles = ntiles_of(g.nt);
+  g.band = kBand;
+  const Decomp d = plan_decomp(w, L.nb_split, device_cus(), static_cast<int>(L.np / 32) * nseg,
+                               kPieceBytes);
+  g.nw = std::min(d.nsplit, kWaveMaxPieces);
+  return g;
+}
+
+template <int KIND, int NSEG>
+sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStream_t st) {
+  WaveArgs v;
+  memset(&v, 0, sizeof(v));
+  v.a[0][0] = a.a_hi;
+  v.a[0][1] = a.a_lo;
+  v.b[0][0] = a.b_hi;
+  v.b[0][1] = a.b_lo;
+  v.a[1][0] = a.a2_hi;
+  v.a[1][1] = a.a2_lo;
+  v.b[1][0] = a.b2_hi;
+  v.b[1][1] = a.b2_lo;
+  v.epi = a.epi;
+  v.dec = a.dec;
+  v.g = wave_grid(w, cover, NSEG);
+  const int threads = std::max(v.g.nw, kWaveMinWaves) * kWave;
+  if (wave_rows(w.L) == 32)
+    k_sym_wave<KIND, 1, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  else
+    k_sym_wave<KIND, 2, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  LAUNCH_TRY();
+  return SP2_OK;
+}
+
 // Trace partial pairs written by one split launch: one per whole tile, one
 // per strip of every split-K tail tile.
 int split_nparts(const Decomp& d) { return d.nfull + kTailStrips * (d.ntiles - d.nfull); }
 
 template <int KIND>
-sp2_status launch_split_t(const WS& w, SplitArgs a, hipStream_t st) {
+sp2_status launch_split_t(const WS& w, SplitArgs a, int64_t cover, hipStream_t st) {
+  if (wave_rows(w.L)) return launch_wave_t<KIND, 1>(w, a, cover, st);
   a.dc = split_decomp<KIND>(w);
   const int ntail = a.dc.ntiles - a.dc.nfull;
   const int grid = a.dc.nfull + ntail * a.dc.nsplit;
@@ -424,7 +481,8 @@ sp2_status launch_split_t(const WS& w, SplitArgs a, hipStream_t st) {
 // (planes in the K-tiled layout).
 sp2_status launch_split(const WS& w, int precision, const uint16_t* ah, const uint16_t* al,
                         const uint16_t* bh, const uint16_t* bl, const Epi& epi, const Decide& dec,
-                        hipStream_t st) {
+                        hipStream_t st, int64_t cover = 0) {
+  if (cover == 0) cover = w.L.np;
   SplitArgs a;
   memset(&a, 0, sizeof(a));
   a.a_hi = ah;
@@ -435,9 +493,9 @@ sp2_status launch_split(const WS& w, int precision, const uint16_t* ah, const ui
   a.epi.oscale = out_scale_of(precision);
   a.dec = dec;
   const int kind = split_kind_of(precision);
-  if (kind == kBF16X3) return launch_split_t<kBF16X3>(w, a, st);
-  if (kind == kBF16X1) return launch_split_t<kBF16X1>(w, a, st);
-  return launch_split_t<kFP16X3>(w, a, st);
+  if (kind == kBF16X3) return launch_split_t<kBF16X3>(w, a, cover, st);
+  if (kind == kBF16X1) return launch_split_t<kBF16X1>(w, a, cover, st);
+  return launch_split_t<kFP16X3>(w, a, cover, st);
 }
 
 // BF16X3 two-segment product out = alpha (X Y + Y X) + beta C of two
@@ -458,10 +516,10 @@ sp2_status launch_split_pair(const WS& w, const uint16_t* xh, const uint16_t* xl
   a.epi = epi;
   a.epi.oscale = 1.0f;
   a.dec = dec;
-  constexpr size_t piece = size_t(256) * 4 * 4 * 16 * 4;
+  if (wave_rows(w.L)) return launch_wave_t<kBF16X3, 2>(w, a, w.L.np, st);
   const int slots = device_cus() * wgs_per_cu(k_sym_split<kBF16X3, 2>, 256);
   a.dc = plan_decomp(w, static_cast<int>(w.L.np / 256), slots, static_cast<int>(w.L.np / 32) * 2,
-                     piece);
+                     kPieceBytes);
   const int ntail = a.dc.ntiles - a.dc.nfull;
   k_sym_split<kBF16X3, 2><<<a.dc.nfull + ntail * a.dc.nsplit, 256, 0, st>>>(a);
   LAUNCH_TRY();
@@ -475,10 +533,9 @@ sp2_status launch_split_pair(const WS& w, const uint16_t* xh, const uint16_t* xl
 
 // Work decomposition of an FP32 product over nseg K segments.
 Decomp f32_decomp(const WS& w, int nseg) {
-  constexpr size_t piece = size_t(256) * 4 * 4 * 16 * 4;   // one 256x256 FP32 accumulator
   const int slots = device_cus() * wgs_per_cu(k_sym_f32, 256);
   return plan_decomp(w, static_cast<int>(w.L.np / 256), slots,
-                     static_cast<int>(w.L.np / 32) * nseg, piece);
+                     static_cast<int>(w.L.np / 32) * nseg, kPieceBytes);
 }
 
 // Launch an FP32 product sum_s A_s B_s^T (nseg <= 4; row-major operands,
@@ -511,9 +568,15 @@ sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float*
   return SP2_OK;
 }
 
+// Trace partial pairs of a product launch (a split one covering `cover` rows).
+int nparts_of_product(const WS& w, int precision, int64_t cover) {
+  if (precision == SP2_FP32) return split_nparts(f32_decomp(w, 1));
+  if (wave_rows(w.L)) return wave_grid(w, cover, 1).ntiles;
+  return split_nparts(split_decomp_of(w, precision));
+}
+
 int nparts_of_layer(const WS& w, int precision, int layer) {
-  if (layer == 0) return w.L.init_blocks;
-  return split_nparts(precision == SP2_FP32 ? f32_decomp(w, 1) : split_decomp_of(w, precision));
+  return layer == 0 ? w.L.init_blocks : nparts_of_product(w, precision, w.L.n);
 }
 
 // Where S_n lives in the forward network (FP32 value and hi/lo planes).
@@ -552,8 +615,9 @@ sp2_status launch_layer(const WS& w, int precision, int n, int mode, const float
   e.centring = kCentredSquare | kCentredOut;
   // The next split layer reads only the planes and the upper triangle of C.
   e.mirror_out = full_out ? 1 : 0;
+  // In place only the n x n part is rewritten: the padding of S stays zero.
   return launch_split(w, precision, w.hi(pair_in), w.lo(pair_in), w.hi(pair_in), w.lo(pair_in), e,
-                      d, st);
+                      d, st, src == dst ? w.L.n : w.L.np);
 }
 
 // Complete an FP32 iterate that split layers left upper-triangle-only.
@@ -1001,9 +1065,9 @@ sp2_status density_impl(const float* H, int64_t n, int64_t ld, int64_t n_occ, co
       return s;
     HIP_TRY(timer.mark(2 * refine_ev + 1, st));
     k_sum_parts<<<1, 256, 0, st>>>(w.ctrl, w.parts[0],
-                                   split_nparts(o.refine == SP2_REFINE_FP32
-                                                    ? f32_decomp(w, 1)
-                                                    : split_decomp_of(w, SP2_FP16X3)));
+                                   nparts_of_product(w, o.refine == SP2_REFINE_FP32 ? SP2_FP32
+                                                                                    : SP2_FP16X3,
+                                                     L.np));
     LAUNCH_TRY();
   } else {
     k_copy_scaled<<<ew_grid(n * n), kEwThreads, 0, st>>>(S, L.np, P, ld, n, n, 1.0f, 0);

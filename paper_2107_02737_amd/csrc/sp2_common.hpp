@@ -100,6 +100,29 @@ __device__ inline double wave_sum(double v) {
   return v;
 }
 
+// Sum over the wave through DPP row shifts and broadcasts (no LDS traffic,
+// about a third of the butterfly's latency), returned to every lane.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, ROWS, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, ROWS, 0xf, false);
+  return v + __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+}
+
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0x111, 0xf>(v);   // row_shr:1, 2, 4, 8: lane 15 of a row holds its sum
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
+  v = dpp_add<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(b), 63);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(b >> 32), 63);
+  return __builtin_bit_cast(double, (uint64_t(hi) << 32) | lo);
+}
+
 __device__ inline double wave_min(double v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v = fmin(v, __shfl_xor(v, off, kWave));
@@ -161,44 +184,34 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double* red) {
 // interval width is small).
 constexpr double kQuadFactor = 16.0;
 
-__device__ __forceinline__ bool stop_test(double t1, double e, int n, const double* err_hist,
-                                          double n_occ, double tol, int stop_rule,
-                                          double stall_gate, int stall_from) {
+// ep = e_{n-2} (err_before).
+__device__ __forceinline__ double err_before(const double* err_hist, int n) {
+  return n >= 2 ? err_hist[n - 2] : 0.0;
+}
+
+__device__ __forceinline__ bool stop_test(double t1, double e, int n, double ep, double n_occ,
+                                          double tol, int stop_rule, double stall_gate,
+                                          int stall_from) {
   if (!(fabs(t1 - n_occ) < 0.5)) return false;
   if (e < tol) return true;
   if (!(stop_rule == 1 && n >= 2 && n - 2 >= stall_from && e < stall_gate)) return false;
-  const double ep = err_hist[n - 2];
   return e >= fmin(ep, kQuadFactor * ep * ep);
 }
 
-template <int NT>
-__device__ __forceinline__ LayerCoef decide_layer(const Decide& d, double* red) {
-  if (d.mode == 2 || d.mode == 3) return hist_coef(d.hist, d.layer, d.mode == 2);
-  if (d.mode != 1) return LayerCoef{1, 1.0f, 0.0f, 0.0f};
-  // One read of the stop flag per work-group, shared through LDS, so that
-  // all of its waves take the same exit -- before the partial sums, so that
-  // launches queued after the stop leave at once.
-  __shared__ int s_stopped;
-  if (threadIdx.x == 0) s_stopped = __atomic_load_n(&d.ctrl->stopped, __ATOMIC_RELAXED);
-  __syncthreads();
-  if (s_stopped) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
-  double t1 = 0.0, t2 = 0.0;
-  for (int i = threadIdx.x; i < d.nparts_in; i += NT) {
-    t1 += d.parts_in[2 * i];
-    t2 += d.parts_in[2 * i + 1];
-  }
-  block_sum2<NT>(t1, t2, red);
+// The decision for layer n from the traces of S_n, recorded by work-group 0;
+// sched: the coefficients of a scheduled layer (used for n < acc_len only).
+__device__ __forceinline__ LayerCoef decide_from_sums(const Decide& d, double t1, double t2,
+                                                      int acc_len, int stall_from, double ep,
+                                                      const LayerCoef& sched) {
   const int n = d.layer;
   const double e = fabs(t1 - t2);
-  const bool stop = stop_test(t1, e, n, d.hist->err, d.n_occ, d.tol, d.stop_rule, d.stall_gate,
-                              d.ctrl->stall_from);
+  const bool stop = stop_test(t1, e, n, ep, d.n_occ, d.tol, d.stop_rule, d.stall_gate, stall_from);
   // Layers of the accelerated schedule (written before the first layer)
   // take their recorded coefficients; the others the trace-closest sign:
   // Tr(S^2) = t2 versus Tr(2S - S^2) = 2 t1 - t2; ties take S^2.  At the
   // end of a schedule every eigenvalue sits on its side, so a trace more
   // than 1/2 from n_occ means the estimates were wrong: the network ends
   // unconverged (acc_failed) and the host runs the plain network instead.
-  const int acc_len = d.ctrl->acc_len;
   const bool scheduled = n < acc_len;
   const bool failed = !stop && acc_len > 0 && n == acc_len && !(fabs(t1 - d.n_occ) < 0.5);
   const int sign = (fabs(t2 - d.n_occ) <= fabs(2.0 * t1 - t2 - d.n_occ)) ? 1 : -1;
@@ -219,7 +232,31 @@ __device__ __forceinline__ LayerCoef decide_layer(const Decide& d, double* red) 
     }
   }
   if (stop || failed) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
-  return scheduled ? hist_coef(d.hist, n, true) : plain_coef(sign);
+  return scheduled ? sched : plain_coef(sign);
+}
+
+template <int NT>
+__device__ __forceinline__ LayerCoef decide_layer(const Decide& d, double* red) {
+  if (d.mode == 2 || d.mode == 3) return hist_coef(d.hist, d.layer, d.mode == 2);
+  if (d.mode != 1) return LayerCoef{1, 1.0f, 0.0f, 0.0f};
+  // One read of the stop flag per work-group, shared through LDS, so that
+  // all of its waves take the same exit -- before the partial sums, so that
+  // launches queued after the stop leave at once.
+  __shared__ int s_stopped;
+  if (threadIdx.x == 0) s_stopped = __atomic_load_n(&d.ctrl->stopped, __ATOMIC_RELAXED);
+  __syncthreads();
+  if (s_stopped) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  double t1 = 0.0, t2 = 0.0;
+  for (int i = threadIdx.x; i < d.nparts_in; i += NT) {
+    t1 += d.parts_in[2 * i];
+    t2 += d.parts_in[2 * i + 1];
+  }
+  block_sum2<NT>(t1, t2, red);
+  const int acc_len = d.ctrl->acc_len;
+  return decide_from_sums(d, t1, t2, acc_len, d.ctrl->stall_from,
+                          err_before(d.hist->err, d.layer),
+                          d.layer < acc_len ? hist_coef(d.hist, d.layer, true)
+                                            : LayerCoef{0, 0.0f, 0.0f, 0.0f});
 }
 
 // The coefficients of a layer as recorded by that layer's product launch,
@@ -250,6 +287,29 @@ __device__ inline void split_fp16s(float x, uint16_t& hi, uint16_t& lo) {
   const _Float16 l = static_cast<_Float16>(xs - static_cast<float>(h));
   hi = __builtin_bit_cast(uint16_t, h);
   lo = __builtin_bit_cast(uint16_t, l);
+}
+
+// The same two at a time, packed into one 32-bit word per plane (the
+// conversions of a pair are one instruction).
+__device__ __forceinline__ void split_pair(float x0, float x1, int kind, uint32_t& hi, uint32_t& lo) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  f32x2 x = {x0, x1};
+  if (kind == 1) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    const bf16x2 h = __builtin_convertvector(x, bf16x2);
+    const f32x2 r = {x0 - static_cast<float>(h[0]), x1 - static_cast<float>(h[1])};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, bf16x2));
+  } else {
+#pragma clang fp contract(off)
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    constexpr float s = float(1 << kFp16ScaleLog2);   // exact scaling
+    const float a = x0 * s, b = x1 * s;
+    const f16x2 h = __builtin_convertvector((f32x2{a, b}), f16x2);
+    const f32x2 r = {a - static_cast<float>(h[0]), b - static_cast<float>(h[1])};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -287,29 +347,27 @@ __device__ inline int xcd_remap(int b, int ntiles) {
 }
 
 __device__ __forceinline__ void tile_of(int logical, int nb, int band, int& ti, int& tj) {
-  int r0 = 0;
-  for (;;) {
-    if (r0 >= nb) {   // out of range: cannot happen with grid == tile count
-      ti = tj = 0;
+  for (int r0 = 0; r0 < nb; r0 += band) {
+    const int h = min(band, nb - r0);
+    // the band's triangle (columns r0 .. r0+h-1), then whole columns of h tiles
+    const int tri = h * (h + 1) / 2, count = tri + h * (nb - r0 - h);
+    if (logical < tri) {
+      int j = 0;
+      while (logical > j) logical -= ++j;
+      ti = r0 + logical;
+      tj = r0 + j;
       return;
     }
-    const int r1 = min(r0 + band, nb) - 1;
-    int count = 0;
-    for (int j = r0; j < nb; ++j) count += min(r1, j) - r0 + 1;
     if (logical < count) {
-      for (int j = r0; j < nb; ++j) {
-        const int c = min(r1, j) - r0 + 1;
-        if (logical < c) {
-          ti = r0 + logical;
-          tj = j;
-          return;
-        }
-        logical -= c;
-      }
+      const int q = logical - tri;
+      const int c = h == 4 ? q >> 2 : q / h;   // bands of 4 everywhere but at the end
+      ti = r0 + q - c * h;
+      tj = r0 + h + c;
+      return;
     }
     logical -= count;
-    r0 += band;
   }
+  ti = tj = 0;   // out of range: cannot happen with grid == tile count
 }
 
 }  // namespace sp2

@@ -414,6 +414,9 @@ void k_sym_split(SplitArgs p) {
     beta = (cn & (kCentredSquare | kCentredPair)) ? cf.b + 2.0f * kPlaneCentre * cf.a : cf.b;
     gamma = (cn & kCentredSquare) ? cf.c - kPlaneCentre * kPlaneCentre * cf.a : cf.c;
   }
+  // no load of the decision may be pending in the K loop (the compiler would
+  // wait for it there in every step)
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   const int64_t np = p.epi.np;
   const int KT = static_cast<int>(np / BK);
   int tile, ti, tj, kb, ke, tail, piece;
@@ -695,6 +698,9 @@ void k_sym_f32(F32Args p) {
     beta = (cn & (kCentredSquare | kCentredPair)) ? cf.b + 2.0f * kPlaneCentre * cf.a : cf.b;
     gamma = (cn & kCentredSquare) ? cf.c - kPlaneCentre * kPlaneCentre * cf.a : cf.c;
   }
+  // no load of the decision may be pending in the K loop (the compiler would
+  // wait for it there in every step)
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
   const int64_t np = p.epi.np;
   const int KT = static_cast<int>(np / BK);
   int tile, ti, tj, kb, ke, tail, piece;

@@ -1,0 +1,411 @@
+// Symmetric-output split products of small orders, whose 256 x 256 tiles
+// would leave the machine idle.  A work-group owns one square tile of 32 or 64
+// rows on or above the diagonal and its waves split the K range: every wave
+// computes the whole tile over its own piece, with fragments loaded straight
+// from the K-tiled planes into registers (a fragment is two contiguous
+// 512-byte runs, and no two waves share one, so LDS would only add a copy and a
+// barrier per step).  The waves' partial tiles meet in LDS, a 32-row strip at
+// a time, where the epilogue finishes them: one launch per product, no partial
+// accumulators in memory.  The pieces are those of the split-K plan of the
+// 256 x 256 kernel and are summed in their order, so a product is the same bit
+// for bit as there.  At n = 402 (32-row tiles, 4 waves) a layer takes 8.6 us
+// against 25.8 us in the 256 x 256 kernel and its split-K strip kernel, at
+// n = 1026 17.7 against 35.6 us: a decision head of 2 us, a K loop of 0.3 to 4 us,
+// an epilogue of 2 to 5 us.
+#pragma once
+
+#include "sp2_common.hpp"
+#include "sp2_gemm.hpp"
+
+namespace sp2 {
+
+// Products of a split kind: main term first, the small cross terms after it.
+template <int KIND>
+struct KindTraits {
+  static constexpr int planes = KIND == kBF16X1 ? 1 : 2;
+  static constexpr int products = KIND == kBF16X1 ? 1 : 3;
+};
+
+// Tile schedule of a launch: nt tile rows of 32 MB rows; nw K pieces, one per
+// wave (at least kWaveMinWaves waves, those past nw without a piece); operand rows and columns at or past lim (a multiple of 64) are zero.
+struct WaveGrid {
+  int nt, ntiles, band;
+  int nw;
+  int lim;
+};
+constexpr int kWaveMaxPieces = 12;
+
+struct WaveArgs {
+  const uint16_t* a[2][2];   // [segment][plane]
+  const uint16_t* b[2][2];
+  Epi epi;
+  Decide dec;
+  WaveGrid g;
+};
+
+// plane_off in 32 bits (np < 65536).
+__device__ __forceinline__ uint32_t plane_off32(int i, int k, int np) {
+  const uint32_t blk = uint32_t(i >> 8) * uint32_t(np >> 4) + uint32_t(k >> 4);
+  return blk * 4096u + uint32_t(((k >> 3) & 1) * 2048 + (i & 255) * 8 + (k & 7));
+}
+
+template <int MB>
+struct WaveShape {
+  static constexpr int T = 32 * MB;
+  // LDS: the image [T][LD] (odd stride: rows and columns conflict free) and
+  // one 32-row strip of every wave's partial tile [nw][T][LP]
+  static constexpr int LD = T + 1, LP = 36;
+  static constexpr int kImg = (T * LD + 3) & ~3, kLds = kImg + kWaveMaxPieces * T * LP;
+  static constexpr int Q = MB;   // four-row groups per thread and strip (256 threads at least)
+};
+constexpr int kWaveMinWaves = 4;
+
+// Decision of a layer by every wave for itself, every load issued at once:
+// the stop flag, the control words and the trace partials arrive together
+// (each is a round trip to memory that another XCD wrote), and no barrier is
+// needed.  A wave that reads the flag as work-group 0 of this very launch sets
+// it leaves as the others do: they find the same stop in the same sums.
+__device__ __forceinline__ LayerCoef decide_layer_wave(const Decide& d) {
+  if (d.mode == 2 || d.mode == 3) return hist_coef(d.hist, d.layer, d.mode == 2);
+  if (d.mode != 1) return LayerCoef{1, 1.0f, 0.0f, 0.0f};
+  const int n = d.layer;
+  const int stopped = __atomic_load_n(&d.ctrl->stopped, __ATOMIC_RELAXED);
+  const int acc_len = d.ctrl->acc_len, stall_from = d.ctrl->stall_from;
+  const LayerCoef hc = hist_coef(d.hist, n, true);
+  const double ep = err_before(d.hist->err, n);
+  double t1 = 0.0, t2 = 0.0;
+#pragma clang loop unroll_count(4)
+  for (int i = threadIdx.x & (kWave - 1); i < d.nparts_in; i += kWave) {
+    t1 += d.parts_in[2 * i];
+    t2 += d.parts_in[2 * i + 1];
+  }
+  t1 = wave_total(t1);
+  t2 = wave_total(t2);
+  if (__builtin_amdgcn_readfirstlane(stopped)) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  return decide_from_sums(d, t1, t2, acc_len, stall_from, ep, hc);
+}
+
+template <int KIND>
+__device__ __forceinline__ void mfma_32x32x16(f32x16& acc, u32x4 a, u32x4 b) {
+  if constexpr (KIND == kFP16X3)
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a),
+                                                 __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
+  else
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                  __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+
+template <int KIND, int MB>
+struct WaveFrag {
+  u32x4 a[KindTraits<KIND>::planes][MB];
+  u32x4 b[KindTraits<KIND>::planes][MB];
+};
+
+template <int KIND, int MB>
+__device__ __forceinline__ void wave_products(const WaveFrag<KIND, MB>& f, f32x16 (&acc)[MB][MB]) {
+  constexpr int pa[3] = {0, 0, 1}, pb[3] = {0, 1, 0};   // hi hi, hi lo, lo hi
+#pragma clang loop unroll(full)
+  for (int k = 0; k < KindTraits<KIND>::products; ++k)
+#pragma clang loop unroll(full)
+    for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+      for (int ni = 0; ni < MB; ++ni)
+        mfma_32x32x16<KIND>(acc[mi][ni], f.a[pa[k]][mi], f.b[pb[k]][ni]);
+}
+
+// C of this thread: four rows of one column per group, strip mi of the tile.
+template <int MB>
+__device__ __forceinline__ void wave_load_c(f32x4 (&cv)[WaveShape<MB>::Q], const Epi& p, int R0,
+                                            int C0, int mi) {
+  constexpr int T = WaveShape<MB>::T;
+  const int np = p.np, nt = blockDim.x;
+#pragma clang loop unroll(full)
+  for (int i = 0; i < WaveShape<MB>::Q; ++i) {
+    const int q = threadIdx.x + nt * i, col = C0 + q % T, row = R0 + 32 * mi + q / T * 4;
+    const float* c = p.c + int64_t(row) * np + col;
+    const bool in = p.c && q < 8 * T;
+#pragma clang loop unroll(full)
+    for (int e = 0; e < 4; ++e) cv[i][e] = in ? c[int64_t(e) * np] : 0.0f;
+  }
+}
+
+// Epilogue of one tile, a 32-row strip at a time.  The waves dump their
+// partial rows into LDS transposed ([column][row], four accumulator rows per
+// 16-byte write); a thread then sums the partials of four rows of one column
+// in piece order, applies v = alpha acc + beta C (+ gamma on the real
+// diagonal), stores the FP32 result, adds the traces and leaves v in the image
+// (a diagonal tile takes its upper elements and writes each to both places, so
+// its image is exactly symmetric).  C was loaded before the K loop: a load
+// waits for every store issued before it.  The mirrored FP32 result and the
+// planes are written from the image.  The loops stay rolled: code that runs
+// once per work-group costs its instruction fetch, about a cycle per byte.
+template <int KIND, int MB>
+__device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
+                                              const f32x4 (&cs)[MB][WaveShape<MB>::Q], const Epi& p,
+                                              float as, float beta, float gamma, int R0, int C0,
+                                              int w, int nw, int lane, float* lds, double* red,
+                                              int tile) {
+  using Sh = WaveShape<MB>;
+  constexpr int T = Sh::T, S = Sh::LD, SP = Sh::LP, Q = Sh::Q;
+  const int np = p.np, nv = p.n_valid, NT = blockDim.x;
+  const bool diag = R0 == C0, use_c = beta != 0.0f;
+  const int t = threadIdx.x;
+  float* img = lds;               // [column][S]
+  float* part = lds + Sh::kImg;   // [wave][column][SP]
+  const float oc = (p.centring & kCentredOut) ? kPlaneCentre : 0.0f;
+  double t1 = 0.0, t2 = 0.0;
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi) {
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4*>(part + (w * T + ni * 32 + (lane & 31)) * SP + 8 * q +
+                                  4 * (lane >> 5)) =
+            f32x4{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2],
+                  acc[mi][ni][4 * q + 3]};
+    __syncthreads();
+    f32x4 v[Q];
+#pragma clang loop unroll(full)
+    for (int i = 0; i < Q; ++i) {
+      const int q = t + NT * i, c = q % T, r4 = q / T * 4;
+      if (q >= 8 * T) break;
+      const float* src = part + c * SP + r4;
+      v[i] = *reinterpret_cast<const f32x4*>(src);
+#pragma clang loop unroll_count(2)
+      for (int k = 1; k < nw; ++k) v[i] += *reinterpret_cast<const f32x4*>(src + k * T * SP);
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 4; ++e)
+        v[i][e] = use_c ? fmaf(as, v[i][e], beta * cs[mi][i][e]) : as * v[i][e];
+    }
+#pragma clang loop unroll(full)
+    for (int i = 0; i < Q; ++i) {
+      const int q = t + NT * i, c = q % T, r = 32 * mi + q / T * 4;
+      const int row = R0 + r, col = C0 + c;
+      if (q >= 8 * T) break;
+      float* o = p.out + int64_t(row) * p.ld_out + col;
+      if (!diag) {
+#pragma clang loop unroll(full)
+        for (int e = 0; e < 4; ++e) {
+          img[c * S + r + e] = v[i][e];
+          const double d = static_cast<double>(v[i][e]);
+          t2 += d * d;   // each unordered pair counted once: doubled below
+          if (p.out && row + e < nv && col < nv) o[int64_t(e) * p.ld_out] = v[i][e];
+        }
+      } else {
+#pragma clang loop unroll(full)
+        for (int e = 0; e < 4; ++e) {
+          float x = v[i][e];
+          const bool on = row + e == col, real_on = on && col < p.n_diag;
+          if (row + e <= col) {   // below the diagonal: mirrored from above
+            if (real_on) x += gamma;
+            img[c * S + r + e] = real_on ? x - oc : x;
+            if (!on) img[(r + e) * S + c] = x;
+            const double d = static_cast<double>(x);
+            t1 += on ? d : 0.0;
+            t2 += (on ? 0.5 : 1.0) * d * d;
+            if (p.out && col < nv) o[int64_t(e) * p.ld_out] = x;
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (p.out && p.mirror_out) {
+    // row C0 + c, columns R0 + r .. r + 3
+#pragma clang loop unroll(disable)
+    for (int q = t; q < T * T / 4; q += NT) {
+      const int r = (q % (T / 4)) * 4, c = q / (T / 4);
+      const int row = C0 + c, col = R0 + r;
+      float* o = p.out + int64_t(row) * p.ld_out + col;
+      const float* s = img + c * S + r;
+      if (row >= nv || col >= nv) continue;
+      if (!diag && p.vec_ok && col + 3 < nv) {
+        *reinterpret_cast<f32x4*>(o) = f32x4{s[0], s[1], s[2], s[3]};
+      } else {
+#pragma clang loop unroll(disable)
+        for (int e = 0; e < 4; ++e)
+          if (col + e < nv && (!diag || r + e < c)) o[e] = s[e];
+      }
+    }
+  }
+  // Planes: a thread per row and 8-column chunk (512-byte runs), then, off
+  // the diagonal, the same of the mirror image.
+  if (p.split_out) {
+    constexpr int B = T * T / 8;
+#pragma clang loop unroll_count(2)
+    for (int q0 = t; q0 < (diag ? B : 2 * B); q0 += NT) {
+      const bool mir = q0 >= B;
+      const int q = mir ? q0 - B : q0;
+      const int i = q % T, k = (q / T) * 8;
+      const float* s = mir ? img + i * S + k : img + k * S + i;
+      const int st = mir ? 1 : S;
+      float v[8];
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 8; ++e) v[e] = s[e * st];
+      u32x4 h, l;
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 4; ++e) {
+        uint32_t a, b;
+        split_pair(v[2 * e], v[2 * e + 1], KIND == kFP16X3 ? 2 : 1, a, b);
+        h[e] = a;
+        l[e] = b;
+      }
+      const int row = (mir ? C0 : R0) + i, col = (mir ? R0 : C0) + k;
+      const uint32_t o = plane_off32(row, col, np);
+      *reinterpret_cast<u32x4*>(p.hi_out + o) = h;
+      if constexpr (KindTraits<KIND>::planes > 1) *reinterpret_cast<u32x4*>(p.lo_out + o) = l;
+    }
+  }
+  if (p.parts_out) {
+    t1 = wave_total(t1);
+    t2 = 2.0 * wave_total(t2);
+    if (lane == 0) {
+      red[w] = t1;
+      red[kWaveMaxPieces + w] = t2;
+    }
+    __syncthreads();
+    if (t < 2) {
+      double s = 0.0;
+      for (int k = 0; k < NT / kWave; ++k) s += red[t * kWaveMaxPieces + k];
+      p.parts_out[2 * tile + t] = s;
+    }
+  }
+}
+
+// The tile of this work-group: nw K pieces of an np-wide K range (linear over
+// the segments), one per wave.
+template <int KIND, int MB, int NSEG = 1>
+__global__ __launch_bounds__(kWaveMaxPieces * kWave)
+__attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_sym_wave(WaveArgs p) {
+  using Sh = WaveShape<MB>;
+  // K steps held in registers: 32-row tiles load a whole piece of 8 at once
+  // (one memory latency per product; half with two segments, which would
+  // spill), 64-row ones run a step ahead
+  constexpr int NP = KindTraits<KIND>::planes, ST = MB > 1 ? 2 : NSEG == 1 ? 8 : 4;
+  constexpr int kLoads = 2 * NP * MB, kMfma = KindTraits<KIND>::products * MB * MB;
+  constexpr int kPer = kMfma / kLoads > 0 ? kMfma / kLoads : 1;
+  __shared__ __attribute__((aligned(16))) float lds[Sh::kLds];
+  __shared__ double red[2 * kWaveMaxPieces];
+  const int lane = threadIdx.x & (kWave - 1), nw = p.g.nw;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int np = p.epi.np, lim = p.g.lim;
+  const int tile = xcd_remap(blockIdx.x, p.g.ntiles);
+  int ti, tj;
+  tile_of(tile, p.g.nt, p.g.band, ti, tj);
+  const int R0 = ti * Sh::T, C0 = tj * Sh::T;   // R0 <= C0
+
+  // Byte offset of this lane's 16 bytes of a block row at K step 0 (row
+  // lane % 32 of the block, column chunk lane / 32).
+  const uint32_t panel = static_cast<uint32_t>(np) * 512;   // bytes of a 256-row panel of one plane
+  const uint32_t lo = (lane & 31) * 16 + (lane >> 5) * 4096;
+  uint32_t oa[MB], ob[MB];
+#pragma clang loop unroll(full)
+  for (int i = 0; i < MB; ++i) {
+    const int ra = R0 / 32 + i, rb = C0 / 32 + i;
+    oa[i] = (ra >> 3) * panel + (ra & 7) * 512 + lo;
+    ob[i] = (rb >> 3) * panel + (rb & 7) * 512 + lo;
+  }
+  f32x16 acc[MB][MB];
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+      for (int q = 0; q < 16; ++q) acc[mi][ni][q] = 0.0f;
+
+  // This wave's piece in 16-wide K steps (split_tail's pieces, units of two
+  // steps), and its part of a segment: steps past lim would only add zeros.
+  const int kseg = np / 16, k2 = NSEG * kseg / 2;
+  const int p0 = k2 * w / nw * 2, p1 = k2 * (w + 1) / nw * 2;
+  // (a column past lim: both operands' rows are zero)
+  const int kend = C0 < lim && w < nw ? lim / 16 : 0;
+  auto range = [&](int seg, int& s0, int& s1) {
+    s0 = min(max(p0 - seg * kseg, 0), kend);
+    s1 = max(min(p1 - seg * kseg, kend), s0);
+  };
+  WaveFrag<KIND, MB> f[ST];
+  auto load = [&](WaveFrag<KIND, MB>& g, int seg, int s) {
+    const int64_t ko = int64_t(s) * 8192;
+#pragma clang loop unroll(full)
+    for (int q = 0; q < NP; ++q) {
+      const char* pa = reinterpret_cast<const char*>(p.a[seg][q]) + ko;
+      const char* pb = reinterpret_cast<const char*>(p.b[seg][q]) + ko;
+#pragma clang loop unroll(full)
+      for (int i = 0; i < MB; ++i) {
+        g.a[q][i] = *reinterpret_cast<const u32x4*>(pa + oa[i]);
+        g.b[q][i] = *reinterpret_cast<const u32x4*>(pb + ob[i]);
+      }
+    }
+  };
+  constexpr int kAhead = MB == 1 ? ST : ST - 1;   // steps loaded before the first product
+  auto preload = [&](int seg, int s0, int s1) {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < kAhead; ++i) load(f[i], seg, max(min(s0 + i, s1 - 1), 0));
+  };
+  int s0, s1;
+  range(0, s0, s1);
+  if (s1 > s0) preload(0, s0, s1);
+
+  f32x4 cs[MB][Sh::Q];
+  constexpr bool kEarlyC = MB * NSEG < 4;   // 64-row pairs have no registers left for it
+  if constexpr (kEarlyC)
+#pragma clang loop unroll(full)
+    for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
+
+  const LayerCoef cf = decide_layer_wave(p.dec);
+  if (cf.sign == 0) return;
+  float alpha = p.epi.alpha, beta = p.epi.beta, gamma = p.epi.gamma;
+  if (p.dec.mode != 0) {
+    const int cn = p.epi.centring;
+    alpha = cf.a;
+    beta = (cn & (kCentredSquare | kCentredPair)) ? cf.b + 2.0f * kPlaneCentre * cf.a : cf.b;
+    gamma = (cn & kCentredSquare) ? cf.c - kPlaneCentre * kPlaneCentre * cf.a : cf.c;
+  }
+  // Nothing but the fragments' own loads may be in flight in the K loop: a
+  // load of the decision still pending on some path would make the compiler
+  // drain the queue wherever its register is reused.
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+
+#pragma clang loop unroll(disable)
+  for (int seg = 0; seg < NSEG; ++seg) {
+    if (seg > 0) {
+      range(seg, s0, s1);
+      if (s1 > s0) preload(seg, s0, s1);
+    }
+    if constexpr (MB == 1) {
+      // a longer piece comes ST steps at a time
+      for (int s = s0; s < s1; s += ST) {
+        if (s > s0) preload(seg, s, s1);
+#pragma clang loop unroll(full)
+        for (int u = 0; u < ST; ++u)
+          if (s + u < s1) wave_products<KIND, MB>(f[u], acc);
+      }
+    } else {
+      // step s + u from stage u while the next step loads, one load after
+      // every kPer MFMAs (clamped to the range at its end)
+      for (int s = s0; s < s1; s += ST) {
+#pragma clang loop unroll(full)
+        for (int u = 0; u < ST; ++u) {
+          __builtin_amdgcn_sched_barrier(0);
+          load(f[(u + ST - 1) % ST], seg, min(s + u + ST - 1, s1 - 1));
+          wave_products<KIND, MB>(f[u], acc);
+#pragma clang loop unroll(full)
+          for (int q = 0; q < kLoads; ++q) {
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, kPer, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+  }
+  if constexpr (!kEarlyC)
+#pragma clang loop unroll(full)
+    for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
+  wave_epilogue<KIND, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, nw, lane, lds,
+                          red, tile);
+}
+
+}  // namespace sp2

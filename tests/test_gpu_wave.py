@@ -1,0 +1,97 @@
+"""k_sym_wave (the split products of small orders) at the edges of
+its tile sizes: one layer against the FP64 product of the operands it
+multiplies, and two layers inside a solve, whose recorded traces must be those
+of the returned iterate."""
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import banner, to_dev
+
+pytestmark = pytest.mark.gpu
+
+U32 = 2.0 ** -24
+# one and two tiles; the last and first order of each tile size (32 rows: n <= 704,
+# 64: <= 1984) and of some numbers of K pieces
+ORDERS = [1, 31, 32, 33, 64, 65, 97, 255, 257, 449, 703, 705, 1001, 1281, 1537, 1983, 1985]
+
+
+@pytest.fixture(scope="module")
+def pk():
+    import paper_2107_02737_amd as pk
+    pk.load_library()
+    return pk
+
+
+def _operand(n, seed):
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((n, n), dtype=np.float32) * np.float32(0.3 / np.sqrt(n))
+    x = np.triu(a) + np.triu(a, 1).T
+    x[np.diag_indices(n)] = rng.uniform(0.0, 1.0, n).astype(np.float32)
+    return x
+
+
+def _planes(x32, precision):
+    t = x32.copy()
+    t[np.diag_indices(t.shape[0])] -= np.float32(0.5)
+    if precision == "fp16x3":
+        hi, lo = oracle.split_fp16_scaled(t)
+        scale = 2.0 ** (-2 * oracle.FP16_SPLIT_SCALE_LOG2)
+    else:
+        hi, lo = oracle.split_bf16(t)
+        scale = 1.0
+    if precision == "bf16x1":
+        lo = np.zeros_like(lo)
+    return hi.astype(np.float64), lo.astype(np.float64), scale
+
+
+@pytest.mark.parametrize("n", ORDERS)
+def test_layer_at_tile_edges(pk, n):
+    import torch
+    x32 = _operand(n, n)
+    for k, precision in enumerate(("bf16x3", "fp16x3", "bf16x1")):
+        hi, lo, s = (torch.from_numpy(v).to("cuda") if isinstance(v, np.ndarray) else v
+                     for v in _planes(x32, precision))
+        r = (hi @ hi + hi @ lo + lo @ hi) * s
+        bound = (3 * n + 4) * U32 * (hi.abs() @ hi.abs() + hi.abs() @ lo.abs()
+                                     + lo.abs() @ hi.abs()) * s
+        x = to_dev(x32).double()
+        ld = n + (0, 3, 64)[k]
+        X = torch.zeros(n, ld, device="cuda")[:, :n]
+        X.copy_(to_dev(x32))
+        for sign in (1, -1):
+            banner(f"wave layer {precision} N={n} ld={ld} sign={sign}")
+            Y = torch.full((n, ld), 7.0, device="cuda")
+            pk.sp2_layer(X, precision, sign, Y[:, :n], pk.allocate_workspace(n))
+            a, b = (1.0, 0.0) if sign > 0 else (-1.0, 2.0)
+            ref = a * r + (a + b) * x - 0.25 * a * torch.eye(n, device="cuda", dtype=torch.float64)
+            tol = bound + 2 * U32 * r.abs() + 4 * U32 * x.abs() + 4 * U32 * ref.abs() + U32
+            y = Y[:, :n].double()
+            assert torch.equal(Y[:, :n], Y[:, :n].T)
+            assert bool((Y[:, n:] == 7.0).all())
+            assert bool(((y - ref).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("n", ORDERS[1:])
+def test_traces_are_those_of_the_iterate(pk, n):
+    import torch
+    h = to_dev(_operand(n, 7 * n))
+    for precision in ("bf16x3", "fp16x3", "bf16x1"):
+        banner(f"wave traces {precision} N={n}")
+        P, info = pk.density(h, n // 2, precision=precision, refine="none", max_iter=2, tol=0.0,
+                             stop_rule=0, allow_unconverged=True, return_info=True)
+        hist = pk.sp2_history(info["workspace"])
+        p = P.double()
+        t1, t2 = p.trace().item(), (p * p).sum().item()
+        # FP64 sums of the same FP32 entries in another order
+        assert abs(hist["t1"][2] - t1) <= 1e-12 * n * max(1.0, abs(t1))
+        assert abs(hist["t2"][2] - t2) <= 1e-12 * n * max(1.0, t2)
+        # the two recorded layers in FP64 from the same bounds
+        lo, hi = info["eps_min"], info["eps_max"]
+        s = (hi * torch.eye(n, device="cuda", dtype=torch.float64) - h.double()) / (hi - lo)
+        for a, b, _ in hist["coef"]:
+            s = a * (s @ s) + b * s
+        # operand roundings 2^-8, 2^-16 or 2^-22 of entries whose rows have norm <= 1, twice over
+        u = {"bf16x1": 2.0 ** -8, "bf16x3": 2.0 ** -16, "fp16x3": 2.0 ** -22}[precision]
+        assert (p - s).abs().max().item() <= 8 * (u + 3 * n * U32)
