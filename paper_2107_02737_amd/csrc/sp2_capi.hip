@@ -407,7 +407,9 @@ Decomp split_decomp_of(const WS& w, int precision) {
 // so 32 rows while they make one round of the machine, 64 while they make two.
 // us per FP16X3 layer, 32-row tiles / 64-row / 256 x 256 kernel: n = 402 8.6 /
 // 11.2 / 25.8; n = 750 16.3 / 13.7 / 31; n = 1026 24 / 17.7 / 35.6; n = 1536 - /
-// 33 / 46; n = 1980 - / 43.8 / 59; n = 2046 (three rounds) - / 55 / 60.
+// 33 / 46; n = 1980 - / 43.8 / 59; n = 2046 (three rounds) - / 55 / 60.  FP32
+// layers keep the same lines (k_wave_f32 / 256 x 256 kernel):
+// n = 1026 50 / 79; n = 1984 117 / 141.
 // It depends on the order alone: a launch over n rows leaves padding unwritten
 // that the 256 x 256 kernel would read.
 int wave_rows(const Layout& L) {
@@ -538,6 +540,27 @@ Decomp f32_decomp(const WS& w, int nseg) {
                      static_cast<int>(w.L.np / 32) * nseg, kPieceBytes);
 }
 
+// The same on k_wave_f32 (every row and column of the padded order).
+template <int NSEG>
+sp2_status launch_wave_f32(const WS& w, const F32Args& a, hipStream_t st) {
+  WaveF32Args v;
+  memset(&v, 0, sizeof(v));
+  for (int s = 0; s < NSEG; ++s) {
+    v.a[s] = a.a[s];
+    v.b[s] = a.b[s];
+  }
+  v.epi = a.epi;
+  v.dec = a.dec;
+  v.g = wave_grid(w, w.L.np, NSEG);
+  constexpr int threads = kWaveF32Waves * kWave;
+  if (wave_rows(w.L) == 32)
+    k_wave_f32<1, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  else
+    k_wave_f32<2, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  LAUNCH_TRY();
+  return SP2_OK;
+}
+
 // Launch an FP32 product sum_s A_s B_s^T (nseg <= 4; row-major operands,
 // leading dimension np), then the strip kernel for its split-K tail tiles.
 sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float* const* B,
@@ -551,6 +574,10 @@ sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float*
   a.nseg = nseg;
   a.epi = epi;
   a.dec = dec;
+  if (wave_rows(w.L)) {
+    if (nseg == 1) return launch_wave_f32<1>(w, a, st);
+    return nseg == 2 ? launch_wave_f32<2>(w, a, st) : launch_wave_f32<4>(w, a, st);
+  }
   a.dc = f32_decomp(w, nseg);
   const int ntail = a.dc.ntiles - a.dc.nfull;
   k_sym_f32<<<a.dc.nfull + ntail * a.dc.nsplit, 256, 0, st>>>(a);
@@ -570,8 +597,9 @@ sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float*
 
 // Trace partial pairs of a product launch (a split one covering `cover` rows).
 int nparts_of_product(const WS& w, int precision, int64_t cover) {
-  if (precision == SP2_FP32) return split_nparts(f32_decomp(w, 1));
+  if (precision == SP2_FP32) cover = w.L.np;
   if (wave_rows(w.L)) return wave_grid(w, cover, 1).ntiles;
+  if (precision == SP2_FP32) return split_nparts(f32_decomp(w, 1));
   return split_nparts(split_decomp_of(w, precision));
 }
 

@@ -19,6 +19,9 @@
 
 namespace sp2 {
 
+// Operand kind of the FP32 products (k_wave_f32).
+constexpr int kF32 = 3;
+
 // Products of a split kind: main term first, the small cross terms after it.
 template <int KIND>
 struct KindTraits {
@@ -27,7 +30,8 @@ struct KindTraits {
 };
 
 // Tile schedule of a launch: nt tile rows of 32 MB rows; nw K pieces, one per
-// wave (at least kWaveMinWaves waves, those past nw without a piece); operand rows and columns at or past lim (a multiple of 64) are zero.
+// wave (at least kWaveMinWaves waves, those past nw without a piece); operand
+// rows and columns at or past lim (a multiple of 64) are zero.
 struct WaveGrid {
   int nt, ntiles, band;
   int nw;
@@ -231,7 +235,7 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
   }
   // Planes: a thread per row and 8-column chunk (512-byte runs), then, off
   // the diagonal, the same of the mirror image.
-  if (p.split_out) {
+  if constexpr (KIND != kF32) if (p.split_out) {
     constexpr int B = T * T / 8;
 #pragma clang loop unroll_count(2)
     for (int q0 = t; q0 < (diag ? B : 2 * B); q0 += NT) {
@@ -405,6 +409,258 @@ void k_sym_wave(WaveArgs p) {
 #pragma clang loop unroll(full)
     for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
   wave_epilogue<KIND, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, nw, lane, lds,
+                          red, tile);
+}
+
+// ---------------------------------------------------------------------------
+// FP32 products of small orders, sum_s A_s B_s^T over up to four K segments,
+// on the BF16 matrix cores.  An FP32 value is the sum of three BF16 values
+// h + m + l (8 significant bits each, signed: 26 bits), so
+//   x y = hh + (hm + mh) + (mm + hl + lh) + ...
+// with the terms left out below 2^-26 |x y|, a quarter of the rounding of one
+// FP32 product.  Six 32x32x16 MFMAs (192 cycles) stand for eight FP32 32x32x2
+// ones (512), and the accumulator of hh is rounded once per 16 K instead of
+// eight times; the other five terms have an accumulator of their own, so their
+// sum (2^-8 of the main one) adds no rounding to it.
+//
+// Tiles and epilogue as in k_sym_wave; eight waves, each taking every eighth
+// pair of K steps.  Operands are row-major: a wave
+// copies its own blocks (32 rows x 16 values, 64 contiguous bytes per row) into
+// a private LDS ring with global_load_lds, NS - 1 steps ahead and without
+// barriers; lane (r, h) then reads its eight values of row r, two 16-byte
+// pieces at positions swizzled by the row so that eight consecutive rows use
+// all banks, and splits them in registers while the other wave of its SIMD
+// multiplies.  The bound is the splitting (32-row tiles: 96 VALU instructions
+// for 6 MFMAs) or the MFMAs (64-row tiles).
+//
+// Against the FP32-MFMA kernel of 256 x 256 tiles and its split-K kernel: a
+// layer of n = 1026 50 us (79 before), n = 1536 71 (90), n = 1984 117 (141); an
+// FP32 solve of n = 256 382 us (1000).  Relative error of a layer of n = 1536
+// 1.7e-7 (2.1e-7 before), of an FP32 solve of n = 1026 3.9e-7 (5.5e-7).
+// ---------------------------------------------------------------------------
+
+struct WaveF32Args {
+  const float* a[4];
+  const float* b[4];
+  Epi epi;
+  Decide dec;
+  WaveGrid g;
+};
+
+constexpr int kWaveF32Waves = 8;
+
+// Three BF16 planes of eight FP32 values (an infinite one leaves NaN in m and
+// l: see add_cross).
+__device__ __forceinline__ void split3(const f32x4& x0, const f32x4& x1, u32x4& h, u32x4& m, u32x4& l) {
+  typedef __attribute__((ext_vector_type(2))) float f32x2;
+  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma clang loop unroll(full)
+  for (int e = 0; e < 4; ++e) {
+    const float a = e < 2 ? x0[2 * e] : x1[2 * e - 4], b = e < 2 ? x0[2 * e + 1] : x1[2 * e - 3];
+    const uint32_t hw = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+    const float ra = a - __builtin_bit_cast(float, hw << 16);
+    const float rb = b - __builtin_bit_cast(float, hw & 0xffff0000u);
+    const uint32_t mw = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{ra, rb}), bf16x2));
+    const f32x2 t = {ra - __builtin_bit_cast(float, mw << 16),
+                     rb - __builtin_bit_cast(float, mw & 0xffff0000u)};
+    h[e] = hw;
+    m[e] = mw;
+    l[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));
+  }
+}
+
+// Main and cross sums together.  Where the main sum is not finite (an operand
+// was infinite or NaN, or the sum overflowed) it is the result: the high parts
+// have the signs and zeros of the values themselves.
+__device__ __forceinline__ float add_cross(float acc, float crs) {
+  return fabsf(acc) < INFINITY ? acc + crs : acc;
+}
+
+template <int MB, int NSEG>
+__global__ __launch_bounds__(kWaveF32Waves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_wave_f32(WaveF32Args p) {
+  using Sh = WaveShape<MB>;
+  constexpr int NW = kWaveF32Waves, NS = MB == 1 ? 4 : 2;   // ring slots per wave
+  constexpr int kSlot = MB * 2 * 2048;                      // bytes: A blocks, B blocks
+  constexpr int kCopies = MB * 2 * 2;                       // 1 KB copies per step
+  static_assert((Sh::kImg + NW * Sh::T * Sh::LP) * 4 <= NW * NS * kSlot, "epilogue fits the ring");
+  __shared__ __attribute__((aligned(1024))) float lds[NW * NS * kSlot / 4];
+  __shared__ double red[2 * kWaveMaxPieces];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int np = p.epi.np, lim = p.g.lim;
+  const int tile = xcd_remap(blockIdx.x, p.g.ntiles);
+  int ti, tj;
+  tile_of(tile, p.g.nt, p.g.band, ti, tj);
+  const int R0 = ti * Sh::T, C0 = tj * Sh::T;   // R0 <= C0
+
+  // The tile's K steps, in pairs of 32 values: kp of them in every segment, of
+  // which the sp that hold diagonal entries of the tile's rows or columns come
+  // first, those of all segments together.  Wave w takes pairs w, w + NW, ...:
+  // steps [0, qd) hold diagonal entries, [qd, qn) do not.
+  constexpr int kTP = Sh::T / 32;
+  const int kp = C0 < lim ? lim / 32 : 0;
+  const int sp = kp == 0 ? 0 : ti == tj ? kTP : 2 * kTP;
+  const int nd = NSEG * sp, nr = kp - sp;
+  const int qn = (NSEG * kp - w + NW - 1) / NW * 2, qd = nd > w ? (nd - w + NW - 1) / NW * 2 : 0;
+  // Copy i of a block: rows 16 i + lane / 4, 16-byte piece (lane % 4) of the
+  // row's 64 bytes, which holds values 4 c .. 4 c + 3 with
+  // c = (lane % 4) ^ (row / 2 % 4).
+  const uint32_t src = ((lane & 3) ^ ((lane >> 3) & 3)) * 16;
+  uint32_t oa[MB][2], ob[MB][2];
+#pragma clang loop unroll(full)
+  for (int i = 0; i < MB; ++i)
+#pragma clang loop unroll(full)
+    for (int u = 0; u < 2; ++u) {
+      oa[i][u] = uint32_t(R0 + 32 * i + 16 * u + (lane >> 2)) * np * 4u + src;
+      ob[i][u] = uint32_t(C0 + 32 * i + 16 * u + (lane >> 2)) * np * 4u + src;
+    }
+  const uint32_t ring0 =
+      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)(lds))) +
+      w * (NS * kSlot);
+  auto copy = [&](int q, int slot) {   // step q into slot `slot` mod NS
+    int x = w + (q >> 1) * NW;
+    const bool dg = x < nd;
+    const int ns = dg ? sp : nr;
+    x -= dg ? 0 : nd;
+    const int sg = (NSEG > 1 && x >= ns) + (NSEG > 2 && x >= 2 * ns) + (NSEG > 2 && x >= 3 * ns);
+    x -= sg * ns;
+    if (dg) {
+      x += x < kTP ? R0 / 32 : C0 / 32 - kTP;
+    } else {
+      x += x >= R0 / 32 ? kTP : 0;
+      x += ti != tj && x >= C0 / 32 ? kTP : 0;
+    }
+    const int64_t ko = x * 32 + (q & 1) * 16;
+    const float* ga = (sg == 0 ? p.a[0] : sg == 1 ? p.a[1] : sg == 2 ? p.a[2] : p.a[3]) + ko;
+    const float* gb = (sg == 0 ? p.b[0] : sg == 1 ? p.b[1] : sg == 2 ? p.b[2] : p.b[3]) + ko;
+    const uint32_t m0s = ring0 + (slot & (NS - 1)) * kSlot;
+#pragma clang loop unroll(full)
+    for (int i = 0; i < MB; ++i)
+#pragma clang loop unroll(full)
+      for (int u = 0; u < 2; ++u) {
+        dma_chunk(oa[i][u], ga, m0s + i * 2048 + u * 1024);
+        dma_chunk(ob[i][u], gb, m0s + (MB + i) * 2048 + u * 1024);
+      }
+  };
+  if (qn > 0) {
+#pragma clang loop unroll(full)
+    for (int i = 0; i < NS; ++i) copy(min(i, qn - 1), i);
+  }
+
+  const LayerCoef cf = decide_layer_wave(p.dec);
+  float alpha = p.epi.alpha, beta = p.epi.beta, gamma = p.epi.gamma;
+  if (p.dec.mode != 0) {
+    alpha = cf.a;
+    beta = cf.b;
+    gamma = cf.c;
+  }
+  f32x16 acc[MB][MB], crs[MB][MB];
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+      for (int q = 0; q < 16; ++q) acc[mi][ni][q] = crs[mi][ni][q] = 0.0f;
+  // this lane's two 16-byte pieces of its row (values 8 h .. 8 h + 7) in a block
+  const int r = lane & 31, h2 = (lane >> 5) * 2;
+  const int f0 = r * 64 + ((h2 ^ ((r >> 1) & 3)) * 16), f1 = r * 64 + (((h2 + 1) ^ ((r >> 1) & 3)) * 16);
+  const char* ring = reinterpret_cast<const char*>(lds) + w * (NS * kSlot);
+  wait_vmem_all();   // the decision's loads, and with them the first copies
+  if (cf.sign == 0) return;
+
+  struct Planes {
+    u32x4 a[3][MB], b[3][MB];
+  };
+  auto convert = [&](Planes& f, int q) {   // step q from its slot
+    const char* sl = ring + (q & (NS - 1)) * kSlot;
+#pragma clang loop unroll(full)
+    for (int i = 0; i < MB; ++i) {
+      split3(*reinterpret_cast<const f32x4*>(sl + i * 2048 + f0),
+             *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1), f.a[0][i], f.a[1][i], f.a[2][i]);
+      split3(*reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0),
+             *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1), f.b[0][i], f.b[1][i],
+             f.b[2][i]);
+    }
+  };
+  // The reads of slot q are done: it takes step q + NS (at the end the last step
+  // again, which is not read, so that the count of copies in flight stays).
+  // After it step q + 1 has arrived.
+  auto refill = [&](int q) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    copy(min(q + NS, qn - 1), q);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * kCopies) : "memory");
+  };
+  // The steps with diagonal entries, on the FP32 cores: a BF16 MFMA adds its
+  // products in groups of eight and cuts each off about 2^-25 below the largest
+  // of its group, towards zero.  Beside the product of a diagonal entry the
+  // squares on the diagonal of S S^T would all lose by that, a bias that the
+  // trace collects: over an FP32 solve of n = 256 the recorded traces were off
+  // by up to 1.2e-4; so it is 1.3e-5 (3.0e-5 with FP32 products throughout).  Lane (r, h) feeds value 8 h + e of
+  // row r to product e.
+  for (int q = 0; q < qd; ++q) {
+    const char* sl = ring + (q & (NS - 1)) * kSlot;
+    f32x4 xa[MB][2], xb[MB][2];
+#pragma clang loop unroll(full)
+    for (int i = 0; i < MB; ++i) {
+      xa[i][0] = *reinterpret_cast<const f32x4*>(sl + i * 2048 + f0);
+      xa[i][1] = *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1);
+      xb[i][0] = *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0);
+      xb[i][1] = *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    refill(q);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma clang loop unroll(full)
+    for (int e = 0; e < 8; ++e)
+#pragma clang loop unroll(full)
+      for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+        for (int ni = 0; ni < MB; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[mi][e / 4][e % 4], xb[ni][e / 4][e % 4],
+                                                             acc[mi][ni], 0, 0, 0);
+  }
+  // Step q from cur while step q + 1 is split into nxt.
+  auto step = [&](const Planes& cur, Planes& nxt, int q) {
+    refill(q);
+    __builtin_amdgcn_sched_barrier(0);
+    convert(nxt, q + 1);
+    constexpr int ta[6] = {0, 0, 1, 1, 0, 2}, tb[6] = {0, 1, 0, 1, 2, 0};
+#pragma clang loop unroll(full)
+    for (int k = 0; k < 6; ++k)
+#pragma clang loop unroll(full)
+      for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+        for (int ni = 0; ni < MB; ++ni)
+          mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], cur.a[ta[k]][mi],
+                                 cur.b[tb[k]][ni]);
+    // the reads first, then the conversions spread over the MFMAs
+    __builtin_amdgcn_sched_group_barrier(0x100, 4 * MB, 0);
+#pragma clang loop unroll(full)
+    for (int k = 0; k < 6 * MB * MB; ++k) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, MB == 1 ? 16 : 8, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  Planes f0s, f1s;
+  if (qn > qd) convert(f0s, qd);
+  for (int q = qd; q < qn; q += 2) {
+    step(f0s, f1s, q);
+    step(f1s, f0s, q + 1);
+  }
+  f32x4 cs[MB][Sh::Q];
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+      for (int q = 0; q < 16; ++q) acc[mi][ni][q] = add_cross(acc[mi][ni][q], crs[mi][ni][q]);
+  wait_vmem_all();
+  __syncthreads();   // the rings are free
+  wave_epilogue<kF32, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, NW, lane, lds,
                           red, tile);
 }
 

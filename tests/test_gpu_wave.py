@@ -1,7 +1,8 @@
-"""k_sym_wave (the split products of small orders) at the edges of
-its tile sizes: one layer against the FP64 product of the operands it
-multiplies, and two layers inside a solve, whose recorded traces must be those
-of the returned iterate."""
+"""k_sym_wave and k_wave_f32 (the products of small orders) at the edges of
+their tile sizes: one layer against the FP64 product of the operands it
+multiplies, two layers inside a solve, whose recorded traces must be those
+of the returned iterate, and the two- and four-segment FP32 products of the
+derivatives."""
 
 import numpy as np
 import pytest
@@ -95,3 +96,65 @@ def test_traces_are_those_of_the_iterate(pk, n):
         # operand roundings 2^-8, 2^-16 or 2^-22 of entries whose rows have norm <= 1, twice over
         u = {"bf16x1": 2.0 ** -8, "bf16x3": 2.0 ** -16, "fp16x3": 2.0 ** -22}[precision]
         assert (p - s).abs().max().item() <= 8 * (u + 3 * n * U32)
+
+
+@pytest.mark.parametrize("n", ORDERS)
+def test_fp32_layer_at_tile_edges(pk, n):
+    """The bound of a plain FP32 product (n u sum |a||b|) holds for the product
+    in BF16 triples: what it leaves out is below u / 4 per product."""
+    import torch
+    x32 = _operand(n, 3 * n)
+    x = to_dev(x32).double()
+    r, bound = x @ x, (n + 4) * U32 * (x.abs() @ x.abs())
+    X = torch.zeros(n, n + 5, device="cuda")[:, :n]
+    X.copy_(to_dev(x32))
+    for sign in (1, -1):
+        banner(f"wave layer fp32 N={n} sign={sign}")
+        Y = torch.full((n, n + 5), 7.0, device="cuda")
+        pk.sp2_layer(X, "fp32", sign, Y[:, :n], pk.allocate_workspace(n))
+        ref = r if sign > 0 else 2 * x - r
+        y = Y[:, :n].double()
+        assert torch.equal(Y[:, :n], Y[:, :n].T)
+        assert bool((Y[:, n:] == 7.0).all())
+        assert bool(((y - ref).abs() <= bound + 2 * U32 * (x.abs() + ref.abs())).all())
+
+
+def test_fp32_layer_with_infinities(pk):
+    """An infinite entry spoils its own row and column and nothing else."""
+    import torch
+    n = 130
+    x32 = np.abs(_operand(n, 5)) + np.float32(0.1)
+    x32[7, 90] = x32[90, 7] = np.inf
+    Y = torch.empty(n, n, device="cuda")
+    pk.sp2_layer(to_dev(x32), "fp32", 1, Y, pk.allocate_workspace(n))
+    y = Y.cpu().numpy()
+    hit = np.zeros((n, n), bool)
+    hit[[7, 90]] = hit[:, [7, 90]] = True
+    assert np.all(np.isposinf(y[hit]))
+    assert np.all(np.isfinite(y[~hit]))
+
+
+@pytest.mark.parametrize("n", [33, 257, 703, 1001, 1537])
+def test_fp32_pair_products(pk, n):
+    """Forward derivative with FP32 products (two K segments per layer, four in
+    the refinement) against first-order perturbation theory."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, _ = torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))
+    occ = n // 2
+    e = 0.5 + 1.5 * torch.rand(n, generator=g, device="cuda", dtype=torch.float64)
+    e[:occ] *= -1
+    h = ((q * e) @ q.T.contiguous()).float()
+    h = torch.triu(h) + torch.triu(h, 1).T
+    a = torch.randn(n, n, generator=g, device="cuda")
+    a = torch.triu(a) + torch.triu(a, 1).T
+    banner(f"wave fp32 pairs N={n}")
+    _, p1 = pk.jvp(h, occ, a, precision="fp32")
+    e, v = torch.linalg.eigh(h.double())
+    o, w = v[:, :occ].contiguous(), v[:, occ:].contiguous()
+    c = (o.T.contiguous() @ a.double() @ w) / (e[:occ, None] - e[None, occ:])
+    ref = o @ c @ w.T.contiguous()
+    ref = ref + ref.T
+    rel = ((p1.double() - ref).norm() / ref.norm()).item()
+    # FP32 rounding of some 25 layers, amplified by the mapped gap (1 in about 30)
+    assert rel <= 25 * 30 * U32
