@@ -402,17 +402,20 @@ Decomp split_decomp_of(const WS& w, int precision) {
   return split_decomp<kFP16X3>(w);
 }
 
-// Tile rows (32 or 64) of the k_sym_wave launches of this order, 0 where they
+// K pieces of a split product on k_sym_wave, those of the 256 x 256 kernel.
+int wave_pieces(const Layout& L, int nseg) {
+  WS none{};
+  const Decomp d = plan_decomp(none, L.nb_split, device_cus(), static_cast<int>(L.np / 32) * nseg,
+                               kPieceBytes);
+  return std::min(d.nsplit, kWaveMaxWaves);
+}
+
+// Tile rows (32 or 64) of the k_wave_f32 launches of this order, 0 where they
 // run on the 256 x 256 kernel: a launch of few tiles is bound by its latency,
 // so 32 rows while they make one round of the machine, 64 while they make two.
-// us per FP16X3 layer, 32-row tiles / 64-row / 256 x 256 kernel: n = 402 8.6 /
-// 11.2 / 25.8; n = 750 16.3 / 13.7 / 31; n = 1026 24 / 17.7 / 35.6; n = 1536 - /
-// 33 / 46; n = 1980 - / 43.8 / 59; n = 2046 (three rounds) - / 55 / 60.  FP32
-// layers keep the same lines (k_wave_f32 / 256 x 256 kernel):
-// n = 1026 50 / 79; n = 1984 117 / 141.
-// It depends on the order alone: a launch over n rows leaves padding unwritten
-// that the 256 x 256 kernel would read.
-int wave_rows(const Layout& L) {
+// us per FP32 layer, k_wave_f32 / 256 x 256 kernel: n = 1026 50 / 79; n = 1984
+// 117 / 141.
+int wave_rows_f32(const Layout& L) {
   const int cus = device_cus();
   const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64;
   if (a * (a + 1) / 2 <= std::min(cus, L.max_parts)) return 32;
@@ -420,18 +423,36 @@ int wave_rows(const Layout& L) {
   return 0;
 }
 
+// Tile rows (32, 64 or 96) of the k_sym_wave launches of this order, 0 where
+// they run on the 256 x 256 kernel: as above, and 96 rows in place of a second
+// or third round of 64 if they make one round and their eight waves (a 96-row
+// wave tile takes half the registers of a SIMD) can take a K piece each.  us
+// per FP16X3 layer, 32-row tiles / 64-row / 96-row / 256 x 256 kernel: n = 402
+// 8.6 / 11.2 / - / 25.8; n = 750 16.3 / 13.7 / 23.5 / 31; n = 1026 24 / 17.7 /
+// 25 / 35.6; n = 1536 - / 33 / 35 (12 pieces) / 46; n = 1980 - / 43.3 / 39.8 /
+// 59; n = 2046 - / 55 / 42 / 58.6.
+// It depends on the order alone: a launch over n rows leaves padding unwritten
+// that the 256 x 256 kernel would read.
+int wave_rows(const Layout& L) {
+  const int cus = device_cus(), rows = wave_rows_f32(L);
+  const int64_t b = (L.n + 63) / 64, c = (L.np + 95) / 96;
+  if (rows != 32 && b * (b + 1) / 2 > cus && c * (c + 1) / 2 <= std::min(cus, L.max_parts) &&
+      wave_pieces(L, 1) <= WaveShape<3>::kMaxWaves)
+    return 96;
+  return rows;
+}
+
 // Wave launch covering the first `cover` rows, nseg K segments.
-WaveGrid wave_grid(const WS& w, int64_t cover, int nseg) {
+WaveGrid wave_grid(const WS& w, int T, int64_t cover, int nseg) {
   const Layout& L = w.L;
   WaveGrid g;
-  const int T = wave_rows(L);
+  if (T == 96) cover = L.np;
   g.lim = static_cast<int>(round_up(L.n, 64));
   g.nt = static_cast<int>((std::max<int64_t>(cover, g.lim) + T - 1) / T);
   g.ntiles = ntiles_of(g.nt);
   g.band = kBand;
-  const Decomp d = plan_decomp(w, L.nb_split, device_cus(), static_cast<int>(L.np / 32) * nseg,
-                               kPieceBytes);
-  g.nw = std::min(d.nsplit, kWaveMaxPieces);
+  g.nw = wave_pieces(L, nseg);
+  if (T == 96) g.nw = std::min(g.nw, WaveShape<3>::kMaxWaves);
   return g;
 }
 
@@ -449,12 +470,16 @@ sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStre
   v.b[1][1] = a.b2_lo;
   v.epi = a.epi;
   v.dec = a.dec;
-  v.g = wave_grid(w, cover, NSEG);
-  const int threads = std::max(v.g.nw, kWaveMinWaves) * kWave;
-  if (wave_rows(w.L) == 32)
+  const int T = wave_rows(w.L);
+  v.g = wave_grid(w, T, cover, NSEG);
+  const int threads =
+      std::max(v.g.nw, T == 96 ? WaveShape<3>::kMinWaves : WaveShape<2>::kMinWaves) * kWave;
+  if (T == 32)
     k_sym_wave<KIND, 1, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
-  else
+  else if (T == 64)
     k_sym_wave<KIND, 2, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  else
+    k_sym_wave<KIND, 3, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
   LAUNCH_TRY();
   return SP2_OK;
 }
@@ -551,9 +576,9 @@ sp2_status launch_wave_f32(const WS& w, const F32Args& a, hipStream_t st) {
   }
   v.epi = a.epi;
   v.dec = a.dec;
-  v.g = wave_grid(w, w.L.np, NSEG);
+  v.g = wave_grid(w, wave_rows_f32(w.L), w.L.np, NSEG);
   constexpr int threads = kWaveF32Waves * kWave;
-  if (wave_rows(w.L) == 32)
+  if (wave_rows_f32(w.L) == 32)
     k_wave_f32<1, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
   else
     k_wave_f32<2, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
@@ -574,7 +599,7 @@ sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float*
   a.nseg = nseg;
   a.epi = epi;
   a.dec = dec;
-  if (wave_rows(w.L)) {
+  if (wave_rows_f32(w.L)) {
     if (nseg == 1) return launch_wave_f32<1>(w, a, st);
     return nseg == 2 ? launch_wave_f32<2>(w, a, st) : launch_wave_f32<4>(w, a, st);
   }
@@ -598,7 +623,8 @@ sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float*
 // Trace partial pairs of a product launch (a split one covering `cover` rows).
 int nparts_of_product(const WS& w, int precision, int64_t cover) {
   if (precision == SP2_FP32) cover = w.L.np;
-  if (wave_rows(w.L)) return wave_grid(w, cover, 1).ntiles;
+  const int T = precision == SP2_FP32 ? wave_rows_f32(w.L) : wave_rows(w.L);
+  if (T) return wave_grid(w, T, cover, 1).ntiles;
   if (precision == SP2_FP32) return split_nparts(f32_decomp(w, 1));
   return split_nparts(split_decomp_of(w, precision));
 }

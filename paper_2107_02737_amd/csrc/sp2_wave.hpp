@@ -1,6 +1,6 @@
 // Symmetric-output split products of small orders, whose 256 x 256 tiles
-// would leave the machine idle.  A work-group owns one square tile of 32 or 64
-// rows on or above the diagonal and its waves split the K range: every wave
+// would leave the machine idle.  A work-group owns one square tile of 32, 64
+// or 96 rows on or above the diagonal and its waves split the K range: every wave
 // computes the whole tile over its own piece, with fragments loaded straight
 // from the K-tiled planes into registers (a fragment is two contiguous
 // 512-byte runs, and no two waves share one, so LDS would only add a copy and a
@@ -10,8 +10,12 @@
 // 256 x 256 kernel and are summed in their order, so a product is the same bit
 // for bit as there.  At n = 402 (32-row tiles, 4 waves) a layer takes 8.6 us
 // against 25.8 us in the 256 x 256 kernel and its split-K strip kernel, at
-// n = 1026 17.7 against 35.6 us: a decision head of 2 us, a K loop of 0.3 to 4 us,
-// an epilogue of 2 to 5 us.
+// n = 1026 17.7 against 35.6 us, at n = 2046 (96-row tiles, 7 waves) 42 against
+// 58.6 us.  At 402 and 1026 that is a decision head of 2 us, a K loop of 0.3 to
+// 4 us, an epilogue of 2 to 5 us and the gap between launches; at 2046 the K loop
+// takes 26 us: 389 MB of fragments come out of L2 at 15 TB/s, so a larger tile
+// than the registers hold (9 of 32 x 32 and two K steps, two waves per SIMD)
+// would be needed to go on.
 #pragma once
 
 #include "sp2_common.hpp"
@@ -30,14 +34,13 @@ struct KindTraits {
 };
 
 // Tile schedule of a launch: nt tile rows of 32 MB rows; nw K pieces, one per
-// wave (at least kWaveMinWaves waves, those past nw without a piece); operand
-// rows and columns at or past lim (a multiple of 64) are zero.
+// wave (at least WaveShape::kMinWaves waves, those past nw without a piece);
+// operand rows and columns at or past lim (a multiple of 64) are zero.
 struct WaveGrid {
   int nt, ntiles, band;
   int nw;
   int lim;
 };
-constexpr int kWaveMaxPieces = 12;
 
 struct WaveArgs {
   const uint16_t* a[2][2];   // [segment][plane]
@@ -59,10 +62,12 @@ struct WaveShape {
   // LDS: the image [T][LD] (odd stride: rows and columns conflict free) and
   // one 32-row strip of every wave's partial tile [nw][T][LP]
   static constexpr int LD = T + 1, LP = 36;
-  static constexpr int kImg = (T * LD + 3) & ~3, kLds = kImg + kWaveMaxPieces * T * LP;
-  static constexpr int Q = MB;   // four-row groups per thread and strip (256 threads at least)
+  static constexpr int kMinWaves = MB < 3 ? 4 : 6, kMaxWaves = MB < 3 ? 12 : 8;
+  static constexpr int kImg = (T * LD + 3) & ~3, kLds = kImg + kMaxWaves * T * LP;
+  static constexpr int Q = MB < 3 ? MB : 2;   // four-row groups per thread and strip
+  static_assert(Q * kMinWaves * kWave >= 8 * T, "a strip per pass");
 };
-constexpr int kWaveMinWaves = 4;
+constexpr int kWaveMaxWaves = 12;
 
 // Decision of a layer by every wave for itself, every load issued at once:
 // the stop flag, the control words and the trace partials arrive together
@@ -127,7 +132,7 @@ __device__ __forceinline__ void wave_load_c(f32x4 (&cv)[WaveShape<MB>::Q], const
   for (int i = 0; i < WaveShape<MB>::Q; ++i) {
     const int q = threadIdx.x + nt * i, col = C0 + q % T, row = R0 + 32 * mi + q / T * 4;
     const float* c = p.c + int64_t(row) * np + col;
-    const bool in = p.c && q < 8 * T;
+    const bool in = p.c && q < 8 * T && (MB < 3 || (row < np && col < np));
 #pragma clang loop unroll(full)
     for (int e = 0; e < 4; ++e) cv[i][e] = in ? c[int64_t(e) * np] : 0.0f;
   }
@@ -158,16 +163,23 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
   float* part = lds + Sh::kImg;   // [wave][column][SP]
   const float oc = (p.centring & kCentredOut) ? kPlaneCentre : 0.0f;
   double t1 = 0.0, t2 = 0.0;
-#pragma clang loop unroll(full)
+#pragma clang loop unroll(disable)
   for (int mi = 0; mi < MB; ++mi) {
+    f32x4 cv[Q];
+    float* mine = part + (w * T + (lane & 31)) * SP + 4 * (lane >> 5);
 #pragma clang loop unroll(full)
-    for (int ni = 0; ni < MB; ++ni)
+    for (int m = 0; m < MB; ++m) {   // the strip's registers
+      if (mi != m) continue;
 #pragma clang loop unroll(full)
-      for (int q = 0; q < 4; ++q)
-        *reinterpret_cast<f32x4*>(part + (w * T + ni * 32 + (lane & 31)) * SP + 8 * q +
-                                  4 * (lane >> 5)) =
-            f32x4{acc[mi][ni][4 * q], acc[mi][ni][4 * q + 1], acc[mi][ni][4 * q + 2],
-                  acc[mi][ni][4 * q + 3]};
+      for (int i = 0; i < Q; ++i) cv[i] = cs[m][i];
+#pragma clang loop unroll(full)
+      for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<f32x4*>(mine + ni * 32 * SP + 8 * q) =
+              f32x4{acc[m][ni][4 * q], acc[m][ni][4 * q + 1], acc[m][ni][4 * q + 2],
+                    acc[m][ni][4 * q + 3]};
+    }
     __syncthreads();
     f32x4 v[Q];
 #pragma clang loop unroll(full)
@@ -180,7 +192,9 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
       for (int k = 1; k < nw; ++k) v[i] += *reinterpret_cast<const f32x4*>(src + k * T * SP);
 #pragma clang loop unroll(full)
       for (int e = 0; e < 4; ++e)
-        v[i][e] = use_c ? fmaf(as, v[i][e], beta * cs[mi][i][e]) : as * v[i][e];
+        v[i][e] = use_c ? fmaf(as, v[i][e], beta * cv[i][e]) : as * v[i][e];
+      // rows and columns past np are none (their operands were other rows')
+      if (MB > 2 && (R0 + 32 * mi + r4 >= np || C0 + c >= np)) v[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
 #pragma clang loop unroll(full)
     for (int i = 0; i < Q; ++i) {
@@ -256,6 +270,7 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
         l[e] = b;
       }
       const int row = (mir ? C0 : R0) + i, col = (mir ? R0 : C0) + k;
+      if (MB > 2 && (row >= np || col >= np)) continue;
       const uint32_t o = plane_off32(row, col, np);
       *reinterpret_cast<u32x4*>(p.hi_out + o) = h;
       if constexpr (KindTraits<KIND>::planes > 1) *reinterpret_cast<u32x4*>(p.lo_out + o) = l;
@@ -266,12 +281,12 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
     t2 = 2.0 * wave_total(t2);
     if (lane == 0) {
       red[w] = t1;
-      red[kWaveMaxPieces + w] = t2;
+      red[kWaveMaxWaves + w] = t2;
     }
     __syncthreads();
     if (t < 2) {
       double s = 0.0;
-      for (int k = 0; k < NT / kWave; ++k) s += red[t * kWaveMaxPieces + k];
+      for (int k = 0; k < NT / kWave; ++k) s += red[t * kWaveMaxWaves + k];
       p.parts_out[2 * tile + t] = s;
     }
   }
@@ -280,8 +295,8 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
 // The tile of this work-group: nw K pieces of an np-wide K range (linear over
 // the segments), one per wave.
 template <int KIND, int MB, int NSEG = 1>
-__global__ __launch_bounds__(kWaveMaxPieces * kWave)
-__attribute__((amdgpu_waves_per_eu(3, 3)))
+__global__ __launch_bounds__(WaveShape<MB>::kMaxWaves * kWave)
+__attribute__((amdgpu_waves_per_eu(WaveShape<MB>::kMaxWaves / 4, WaveShape<MB>::kMaxWaves / 4)))
 void k_sym_wave(WaveArgs p) {
   using Sh = WaveShape<MB>;
   // K steps held in registers: 32-row tiles load a whole piece of 8 at once
@@ -291,7 +306,7 @@ void k_sym_wave(WaveArgs p) {
   constexpr int kLoads = 2 * NP * MB, kMfma = KindTraits<KIND>::products * MB * MB;
   constexpr int kPer = kMfma / kLoads > 0 ? kMfma / kLoads : 1;
   __shared__ __attribute__((aligned(16))) float lds[Sh::kLds];
-  __shared__ double red[2 * kWaveMaxPieces];
+  __shared__ double red[2 * kWaveMaxWaves];
   const int lane = threadIdx.x & (kWave - 1), nw = p.g.nw;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int np = p.epi.np, lim = p.g.lim;
@@ -300,16 +315,17 @@ void k_sym_wave(WaveArgs p) {
   tile_of(tile, p.g.nt, p.g.band, ti, tj);
   const int R0 = ti * Sh::T, C0 = tj * Sh::T;   // R0 <= C0
 
-  // Byte offset of this lane's 16 bytes of a block row at K step 0 (row
-  // lane % 32 of the block, column chunk lane / 32).
+  // Byte offset of a block at K step 0, and in it of this lane's 16 bytes (row
+  // lane % 32, column chunk lane / 32).
   const uint32_t panel = static_cast<uint32_t>(np) * 512;   // bytes of a 256-row panel of one plane
   const uint32_t lo = (lane & 31) * 16 + (lane >> 5) * 4096;
   uint32_t oa[MB], ob[MB];
 #pragma clang loop unroll(full)
   for (int i = 0; i < MB; ++i) {
-    const int ra = R0 / 32 + i, rb = C0 / 32 + i;
-    oa[i] = (ra >> 3) * panel + (ra & 7) * 512 + lo;
-    ob[i] = (rb >> 3) * panel + (rb & 7) * 512 + lo;
+    // (96-row tiles may end past np: those blocks take the last one's rows)
+    const int ra = min(R0 / 32 + i, np / 32 - 1), rb = min(C0 / 32 + i, np / 32 - 1);
+    oa[i] = (ra >> 3) * panel + (ra & 7) * 512;
+    ob[i] = (rb >> 3) * panel + (rb & 7) * 512;
   }
   f32x16 acc[MB][MB];
 #pragma clang loop unroll(full)
@@ -338,8 +354,8 @@ void k_sym_wave(WaveArgs p) {
       const char* pb = reinterpret_cast<const char*>(p.b[seg][q]) + ko;
 #pragma clang loop unroll(full)
       for (int i = 0; i < MB; ++i) {
-        g.a[q][i] = *reinterpret_cast<const u32x4*>(pa + oa[i]);
-        g.b[q][i] = *reinterpret_cast<const u32x4*>(pb + ob[i]);
+        g.a[q][i] = *reinterpret_cast<const u32x4*>(pa + oa[i] + lo);
+        g.b[q][i] = *reinterpret_cast<const u32x4*>(pb + ob[i] + lo);
       }
     }
   };
@@ -353,7 +369,7 @@ void k_sym_wave(WaveArgs p) {
   if (s1 > s0) preload(0, s0, s1);
 
   f32x4 cs[MB][Sh::Q];
-  constexpr bool kEarlyC = MB * NSEG < 4;   // 64-row pairs have no registers left for it
+  constexpr bool kEarlyC = MB * NSEG < 3 || MB == 1;   // else no registers are left for it
   if constexpr (kEarlyC)
 #pragma clang loop unroll(full)
     for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
@@ -485,7 +501,7 @@ void k_wave_f32(WaveF32Args p) {
   constexpr int kCopies = MB * 2 * 2;                       // 1 KB copies per step
   static_assert((Sh::kImg + NW * Sh::T * Sh::LP) * 4 <= NW * NS * kSlot, "epilogue fits the ring");
   __shared__ __attribute__((aligned(1024))) float lds[NW * NS * kSlot / 4];
-  __shared__ double red[2 * kWaveMaxPieces];
+  __shared__ double red[2 * kWaveMaxWaves];
   const int lane = threadIdx.x & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int np = p.epi.np, lim = p.g.lim;

@@ -158,3 +158,35 @@ def test_fp32_pair_products(pk, n):
     rel = ((p1.double() - ref).norm() / ref.norm()).item()
     # FP32 rounding of some 25 layers, amplified by the mapped gap (1 in about 30)
     assert rel <= 25 * 30 * U32
+
+
+@pytest.mark.parametrize("n", [1793, 2017, 2047, 2048, 2049])
+def test_96_row_tiles(pk, n):
+    """The first and last orders of the 96-row tiles, whose last row of tiles
+    ends past the padded order, and the order after them."""
+    test_layer_at_tile_edges(pk, n)
+    test_traces_are_those_of_the_iterate(pk, n)
+
+
+@pytest.mark.parametrize("n", [1793, 2047])
+def test_split_pair_of_96_row_tiles(pk, n):
+    """Forward derivative with BF16X3 pair products against first-order
+    perturbation theory; such a product leaves out 2^-17 of its terms (25
+    layers, a mapped gap of 1 in about 30)."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(n)
+    q, _ = torch.linalg.qr(torch.randn(n, n, generator=g, device="cuda", dtype=torch.float64))
+    occ = n // 2
+    e = 0.5 + 1.5 * torch.rand(n, generator=g, device="cuda", dtype=torch.float64)
+    e[:occ] *= -1
+    h = ((q * e) @ q.T.contiguous()).float()
+    h = torch.triu(h) + torch.triu(h, 1).T
+    a = torch.randn(n, n, generator=g, device="cuda")
+    a = torch.triu(a) + torch.triu(a, 1).T
+    banner(f"wave split pairs N={n}")
+    _, p1 = pk.jvp(h, occ, a, precision="bf16x3", split_derivatives=True)
+    o, w = q[:, :occ].contiguous(), q[:, occ:].contiguous()
+    c = (o.T.contiguous() @ a.double() @ w) / (e[:occ, None] - e[None, occ:])
+    ref = o @ c @ w.T.contiguous()
+    ref = ref + ref.T
+    assert ((p1.double() - ref).norm() / ref.norm()).item() <= 25 * 30 * 2.0 ** -17
