@@ -456,8 +456,7 @@ WaveGrid wave_grid(const WS& w, int T, int64_t cover, int nseg) {
   return g;
 }
 
-template <int KIND, int NSEG>
-sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStream_t st) {
+WaveArgs wave_args(const SplitArgs& a) {
   WaveArgs v;
   memset(&v, 0, sizeof(v));
   v.a[0][0] = a.a_hi;
@@ -470,6 +469,12 @@ sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStre
   v.b[1][1] = a.b2_lo;
   v.epi = a.epi;
   v.dec = a.dec;
+  return v;
+}
+
+template <int KIND, int NSEG>
+sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStream_t st) {
+  WaveArgs v = wave_args(a);
   const int T = wave_rows(w.L);
   v.g = wave_grid(w, T, cover, NSEG);
   const int threads =
@@ -484,6 +489,26 @@ sp2_status launch_wave_t(const WS& w, const SplitArgs& a, int64_t cover, hipStre
   return SP2_OK;
 }
 
+// 192 x 192 tiles (k_sym_mid): where the 256 x 256 ones are too many to be split
+// along K (more than half a round) and 192 x 192 ones make one round, a round of
+// 0.56 times the work.  us per FP16X3 layer, 192 / 256: n = 4092 197 / 254.5.
+bool mid_tiles(const Layout& L) {
+  const int cus = device_cus();
+  const int64_t c = (L.np + kMidRows - 1) / kMidRows;
+  return L.ntiles_split > cus / 2 && c * (c + 1) / 2 <= std::min(cus, L.max_parts);
+}
+
+template <int KIND, int NSEG>
+sp2_status launch_mid_t(const WS& w, const SplitArgs& a, hipStream_t st) {
+  WaveArgs v = wave_args(a);
+  v.g.nt = static_cast<int>((w.L.np + kMidRows - 1) / kMidRows);
+  v.g.ntiles = ntiles_of(v.g.nt);
+  v.g.band = kBand;
+  k_sym_mid<KIND, NSEG><<<v.g.ntiles, 256, 0, st>>>(v);
+  LAUNCH_TRY();
+  return SP2_OK;
+}
+
 // Trace partial pairs written by one split launch: one per whole tile, one
 // per strip of every split-K tail tile.
 int split_nparts(const Decomp& d) { return d.nfull + kTailStrips * (d.ntiles - d.nfull); }
@@ -491,6 +516,7 @@ int split_nparts(const Decomp& d) { return d.nfull + kTailStrips * (d.ntiles - d
 template <int KIND>
 sp2_status launch_split_t(const WS& w, SplitArgs a, int64_t cover, hipStream_t st) {
   if (wave_rows(w.L)) return launch_wave_t<KIND, 1>(w, a, cover, st);
+  if (mid_tiles(w.L)) return launch_mid_t<KIND, 1>(w, a, st);
   a.dc = split_decomp<KIND>(w);
   const int ntail = a.dc.ntiles - a.dc.nfull;
   const int grid = a.dc.nfull + ntail * a.dc.nsplit;
@@ -544,6 +570,7 @@ sp2_status launch_split_pair(const WS& w, const uint16_t* xh, const uint16_t* xl
   a.epi.oscale = 1.0f;
   a.dec = dec;
   if (wave_rows(w.L)) return launch_wave_t<kBF16X3, 2>(w, a, w.L.np, st);
+  if (mid_tiles(w.L)) return launch_mid_t<kBF16X3, 2>(w, a, st);
   const int slots = device_cus() * wgs_per_cu(k_sym_split<kBF16X3, 2>, 256);
   a.dc = plan_decomp(w, static_cast<int>(w.L.np / 256), slots, static_cast<int>(w.L.np / 32) * 2,
                      kPieceBytes);
@@ -626,6 +653,7 @@ int nparts_of_product(const WS& w, int precision, int64_t cover) {
   const int T = precision == SP2_FP32 ? wave_rows_f32(w.L) : wave_rows(w.L);
   if (T) return wave_grid(w, T, cover, 1).ntiles;
   if (precision == SP2_FP32) return split_nparts(f32_decomp(w, 1));
+  if (mid_tiles(w.L)) return static_cast<int>(ntiles_of((w.L.np + kMidRows - 1) / kMidRows));
   return split_nparts(split_decomp_of(w, precision));
 }
 

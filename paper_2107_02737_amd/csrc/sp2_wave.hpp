@@ -138,6 +138,87 @@ __device__ __forceinline__ void wave_load_c(f32x4 (&cv)[WaveShape<MB>::Q], const
   }
 }
 
+// What follows from the finished image of a tile (element (row, column) at
+// column * CS + row * RS): the mirrored FP32 result, the planes, and the tile's
+// trace pair.
+template <int KIND, int T, int CS, int RS>
+__device__ __forceinline__ void tile_finish(const Epi& p, int R0, int C0, int w, int lane,
+                                            const float* img, double* red, int tile, double t1,
+                                            double t2) {
+  const int np = p.np, nv = p.n_valid, NT = blockDim.x, t = threadIdx.x;
+  const bool diag = R0 == C0;
+  if (p.out && p.mirror_out) {
+    // row C0 + c, columns R0 + r .. r + 3
+#pragma clang loop unroll(disable)
+    for (int q = t; q < T * T / 4; q += NT) {
+      const int r = (q % (T / 4)) * 4, c = q / (T / 4);
+      const int row = C0 + c, col = R0 + r;
+      float* o = p.out + int64_t(row) * p.ld_out + col;
+      const float* s = img + c * CS + r * RS;
+      if (row >= nv || col >= nv) continue;
+      if (!diag && p.vec_ok && col + 3 < nv) {
+        *reinterpret_cast<f32x4*>(o) = f32x4{s[0], s[RS], s[2 * RS], s[3 * RS]};
+      } else {
+#pragma clang loop unroll(disable)
+        for (int e = 0; e < 4; ++e)
+          if (col + e < nv && (!diag || r + e < c)) o[e] = s[e * RS];
+      }
+    }
+  }
+  // Planes: a thread per row and 8-column chunk (512-byte runs), then, off
+  // the diagonal, the same of the mirror image.
+  if constexpr (KIND != kF32) if (p.split_out) {
+    constexpr int B = T * T / 8;
+#pragma clang loop unroll_count(2)
+    for (int q0 = t; q0 < (diag ? B : 2 * B); q0 += NT) {
+      const bool mir = q0 >= B;
+      const int q = mir ? q0 - B : q0;
+      const int i = q % T, k = (q / T) * 8;
+      const float* s = mir ? img + i * CS + k * RS : img + k * CS + i * RS;
+      const int st = mir ? RS : CS;
+      float v[8];
+      if (CS == 1 && !mir) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(s), y = *reinterpret_cast<const f32x4*>(s + 4);
+#pragma clang loop unroll(full)
+        for (int e = 0; e < 4; ++e) {
+          v[e] = x[e];
+          v[4 + e] = y[e];
+        }
+      } else {
+#pragma clang loop unroll(full)
+        for (int e = 0; e < 8; ++e) v[e] = s[e * st];
+      }
+      u32x4 h, l;
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 4; ++e) {
+        uint32_t a, b;
+        split_pair(v[2 * e], v[2 * e + 1], KIND == kFP16X3 ? 2 : 1, a, b);
+        h[e] = a;
+        l[e] = b;
+      }
+      const int row = (mir ? C0 : R0) + i, col = (mir ? R0 : C0) + k;
+      if (T > 64 && (row >= np || col >= np)) continue;
+      const uint32_t o = plane_off32(row, col, np);
+      *reinterpret_cast<u32x4*>(p.hi_out + o) = h;
+      if constexpr (KindTraits<KIND>::planes > 1) *reinterpret_cast<u32x4*>(p.lo_out + o) = l;
+    }
+  }
+  if (p.parts_out) {
+    t1 = wave_total(t1);
+    t2 = 2.0 * wave_total(t2);
+    if (lane == 0) {
+      red[w] = t1;
+      red[kWaveMaxWaves + w] = t2;
+    }
+    __syncthreads();
+    if (t < 2) {
+      double s = 0.0;
+      for (int k = 0; k < NT / kWave; ++k) s += red[t * kWaveMaxWaves + k];
+      p.parts_out[2 * tile + t] = s;
+    }
+  }
+}
+
 // Epilogue of one tile, a 32-row strip at a time.  The waves dump their
 // partial rows into LDS transposed ([column][row], four accumulator rows per
 // 16-byte write); a thread then sums the partials of four rows of one column
@@ -229,67 +310,7 @@ __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
     }
     __syncthreads();
   }
-  if (p.out && p.mirror_out) {
-    // row C0 + c, columns R0 + r .. r + 3
-#pragma clang loop unroll(disable)
-    for (int q = t; q < T * T / 4; q += NT) {
-      const int r = (q % (T / 4)) * 4, c = q / (T / 4);
-      const int row = C0 + c, col = R0 + r;
-      float* o = p.out + int64_t(row) * p.ld_out + col;
-      const float* s = img + c * S + r;
-      if (row >= nv || col >= nv) continue;
-      if (!diag && p.vec_ok && col + 3 < nv) {
-        *reinterpret_cast<f32x4*>(o) = f32x4{s[0], s[1], s[2], s[3]};
-      } else {
-#pragma clang loop unroll(disable)
-        for (int e = 0; e < 4; ++e)
-          if (col + e < nv && (!diag || r + e < c)) o[e] = s[e];
-      }
-    }
-  }
-  // Planes: a thread per row and 8-column chunk (512-byte runs), then, off
-  // the diagonal, the same of the mirror image.
-  if constexpr (KIND != kF32) if (p.split_out) {
-    constexpr int B = T * T / 8;
-#pragma clang loop unroll_count(2)
-    for (int q0 = t; q0 < (diag ? B : 2 * B); q0 += NT) {
-      const bool mir = q0 >= B;
-      const int q = mir ? q0 - B : q0;
-      const int i = q % T, k = (q / T) * 8;
-      const float* s = mir ? img + i * S + k : img + k * S + i;
-      const int st = mir ? 1 : S;
-      float v[8];
-#pragma clang loop unroll(full)
-      for (int e = 0; e < 8; ++e) v[e] = s[e * st];
-      u32x4 h, l;
-#pragma clang loop unroll(full)
-      for (int e = 0; e < 4; ++e) {
-        uint32_t a, b;
-        split_pair(v[2 * e], v[2 * e + 1], KIND == kFP16X3 ? 2 : 1, a, b);
-        h[e] = a;
-        l[e] = b;
-      }
-      const int row = (mir ? C0 : R0) + i, col = (mir ? R0 : C0) + k;
-      if (MB > 2 && (row >= np || col >= np)) continue;
-      const uint32_t o = plane_off32(row, col, np);
-      *reinterpret_cast<u32x4*>(p.hi_out + o) = h;
-      if constexpr (KindTraits<KIND>::planes > 1) *reinterpret_cast<u32x4*>(p.lo_out + o) = l;
-    }
-  }
-  if (p.parts_out) {
-    t1 = wave_total(t1);
-    t2 = 2.0 * wave_total(t2);
-    if (lane == 0) {
-      red[w] = t1;
-      red[kWaveMaxWaves + w] = t2;
-    }
-    __syncthreads();
-    if (t < 2) {
-      double s = 0.0;
-      for (int k = 0; k < NT / kWave; ++k) s += red[t * kWaveMaxWaves + k];
-      p.parts_out[2 * tile + t] = s;
-    }
-  }
+  tile_finish<KIND, T, S, 1>(p, R0, C0, w, lane, img, red, tile, t1, t2);
 }
 
 // The tile of this work-group: nw K pieces of an np-wide K range (linear over
@@ -426,6 +447,245 @@ void k_sym_wave(WaveArgs p) {
     for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
   wave_epilogue<KIND, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, nw, lane, lds,
                           red, tile);
+}
+
+// ---------------------------------------------------------------------------
+// Split products on 192 x 192 tiles: the scheme of k_sym_split (four waves,
+// here of 96 x 96; LDS ring of K steps filled by copies, fragments double
+// buffered in registers, one barrier per step) for orders whose 256 x 256
+// tiles, unsplit, would use little more than half the machine.  Wave w copies
+// plane w of a step (A hi, A lo, B hi, B lo; 64 rows of one 8-column chunk per
+// copy).  The K order is that of k_sym_split, so results are the same bit for
+// bit.  C is loaded during the last K steps (the accumulators leave 512 - 240
+// registers for it): behind the K loop, in batches with the stores between,
+// it took 31 us instead of 6.  The finished values go through an FP32 image of
+// the whole tile in LDS ([row][196]: rows are read in 16-byte pieces, columns by
+// consecutive lanes, both without bank conflicts).
+//
+// A layer of n = 4092 takes 197 us against 254.5 us on 136 tiles of 256 x 256:
+// 167 us of K loop, which runs at 93% of the MFMA rate of a clock that the power
+// limit holds at 1.4 GHz (1340 TFLOP/s over the padded tiles, what a large
+// library product reaches), 17 us of epilogue at some 4 TB/s, and the launch.
+// ---------------------------------------------------------------------------
+constexpr int kMidRows = 192;
+
+template <int KIND, int NSEG = 1>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void k_sym_mid(WaveArgs p) {
+  constexpr int T = kMidRows, S = T + 4, NS = 4, M = 3;   // image [row][S]
+  constexpr bool kLo = KIND != kBF16X1;
+  constexpr int kPlane = T * 32, kSlot = (kLo ? 4 : 2) * kPlane;   // bytes per K step
+  constexpr int kCopies = kLo ? 6 : 3;                             // per wave and K step
+  __shared__ __attribute__((aligned(1024))) float lds[T * S];
+  static_assert(NS * kSlot <= int(sizeof(lds)), "ring exceeds the image");
+  __shared__ double red[2 * kWaveMaxWaves];
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int np = p.epi.np, KT = np / 16, ke = NSEG * KT;
+  const int tile = xcd_remap(blockIdx.x, p.g.ntiles);
+  int ti, tj;
+  tile_of(tile, p.g.nt, p.g.band, ti, tj);
+  const int R0 = ti * T, C0 = tj * T;
+
+  // This wave's copies of a K step: chunk h, row group g of plane pl (tiles may
+  // end past np: those groups take the last rows).
+  const int pl = kLo ? w : w >> 1;   // kLo: A hi, A lo, B hi, B lo; else A, B
+  const bool isb = kLo ? pl >= 2 : pl == 1;
+  const int q = kLo ? pl & 1 : 0;
+  uint32_t go[3];
+#pragma clang loop unroll(full)
+  for (int g = 0; g < 3; ++g) {
+    const int row = min((isb ? C0 : R0) + 64 * g, np - 64);
+    go[g] = uint32_t(row >> 8) * uint32_t(np) * 512u + (row & 255) * 16u;
+  }
+  const uint32_t lds0 = static_cast<uint32_t>(
+      reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)(lds)));
+  const uint32_t v0 = lane * 16;
+  const uint16_t* seg0 = isb ? (q ? p.b[0][1] : p.b[0][0]) : (q ? p.a[0][1] : p.a[0][0]);
+  const uint16_t* seg1 = isb ? (q ? p.b[1][1] : p.b[1][0]) : (q ? p.a[1][1] : p.a[1][0]);
+  auto source = [&](int k) {
+    const bool sg = NSEG == 2 && k >= KT;
+    return reinterpret_cast<const char*>(sg ? seg1 : seg0) + int64_t(sg ? k - KT : k) * 8192;
+  };
+  auto copy = [&](const char* src, int slot, int i) {   // copy i of a K step
+    const int h = kLo ? i / 3 : w & 1, g = kLo ? i % 3 : i;
+    dma_chunk(v0 + h * 4096, src + go[g], lds0 + slot * kSlot + pl * kPlane + (h * 3 + g) * 1024);
+  };
+#pragma clang loop unroll(full)
+  for (int k = 0; k < NS; ++k) {
+    const char* src = source(min(k, ke - 1));
+#pragma clang loop unroll(full)
+    for (int i = 0; i < kCopies; ++i) copy(src, k, i);
+  }
+
+  const LayerCoef cf = decide_layer_wave(p.dec);
+  float alpha = p.epi.alpha, beta = p.epi.beta, gamma = p.epi.gamma;
+  if (p.dec.mode != 0) {
+    const int cn = p.epi.centring;
+    alpha = cf.a;
+    beta = (cn & (kCentredSquare | kCentredPair)) ? cf.b + 2.0f * kPlaneCentre * cf.a : cf.b;
+    gamma = (cn & kCentredSquare) ? cf.c - kPlaneCentre * kPlaneCentre * cf.a : cf.c;
+  }
+  // the decision's loads, and with them the first copies (a wait that the
+  // compiler knows, or it would wait for a register of the decision in the loop)
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  if (cf.sign == 0) return;
+  __syncthreads();
+
+  f32x16 acc[M][M];
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < M; ++mi)
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < M; ++ni)
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.0f;
+  const int wm = w >> 1, wn = w & 1, r = lane & 31, h = lane >> 5;
+  const int fa = h * 3072 + (wm * 96 + r) * 16;
+  const int fb = (kLo ? 2 : 1) * kPlane + h * 3072 + (wn * 96 + r) * 16;
+  const char* ring = reinterpret_cast<const char*>(lds);
+  using Frag = WaveFrag<KIND, M>;
+  constexpr int kReads = 2 * KindTraits<KIND>::planes * M;
+  auto read = [&](Frag& f, int slot, int i) {   // fragment i of a K step
+    const char* sl = ring + slot * kSlot + (i / (2 * M)) * kPlane + (i % M) * 512;
+    if (i % (2 * M) < M)
+      f.a[i / (2 * M)][i % M] = *reinterpret_cast<const u32x4*>(sl + fa);
+    else
+      f.b[i / (2 * M)][i % M] = *reinterpret_cast<const u32x4*>(sl + fb);
+  };
+  // Step k from cur while step k + 1 is read into nxt, a read after each of the
+  // first MFMAs; before the last NS steps slot k takes step k + NS, a copy after
+  // each of the next MFMAs.
+  auto products = [&](const Frag& cur, Frag& nxt, int k, bool refill) {
+    const char* src = source(k + NS);
+    constexpr int pa[3] = {0, 0, 1}, pb[3] = {0, 1, 0};   // hi hi, hi lo, lo hi
+    __syncthreads();
+#pragma clang loop unroll(full)
+    for (int j = 0; j < KindTraits<KIND>::products * M * M; ++j) {
+      const int u = j / (M * M), mi = j / M % M, ni = j % M;
+      mfma_32x32x16<KIND>(acc[mi][ni], cur.a[pa[u]][mi], cur.b[pb[u]][ni]);
+      if (j < kReads) read(nxt, (k + 1) & (NS - 1), j);
+      else if (refill && j - kReads < kCopies) copy(src, k & (NS - 1), j - kReads);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto step = [&](const Frag& cur, Frag& nxt, int k) {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((NS - 2) * kCopies) : "memory");
+    products(cur, nxt, k, true);
+  };
+  auto last_step = [&](const Frag& cur, Frag& nxt, int k) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    products(cur, nxt, k, false);
+  };
+  Frag f0, f1;
+#pragma clang loop unroll(full)
+  for (int i = 0; i < kReads; ++i) read(f0, 0, i);
+#pragma clang loop unroll(disable)
+  for (int k = 0; k < ke - NS; k += 2) {
+    step(f0, f1, k);
+    step(f1, f0, k + 1);
+  }
+  // The last NS steps, all copied, with C on its way: four columns of one row
+  // per load (a launch without C reads one row of A instead).
+  wait_vmem_all();
+  // Block (i, j): rows 16 i + 4 w + lane / 16, columns 64 j + 4 (lane % 16).
+  const Epi& ep = p.epi;
+  const bool diag = R0 == C0, use_c = beta != 0.0f && ep.c;
+  const int er = 4 * w + (lane >> 4), ec = (lane & 15) * 4;
+  const float* cb = use_c ? ep.c : reinterpret_cast<const float*>(p.a[0][0]);
+  const uint32_t cof = use_c ? uint32_t(er) * np + ec : ec;
+  f32x4 c[T / 16][3];
+#pragma clang loop unroll(full)
+  for (int i = 0; i < T / 16; ++i)
+#pragma clang loop unroll(full)
+    for (int j = 0; j < 3; ++j) {
+      const float* blk = cb + (use_c ? int64_t(min(R0 + 16 * i, np - 16)) * np : 0) +
+                         min(C0 + 64 * j, np - 64);
+      c[i][j] = *reinterpret_cast<const f32x4*>(blk + cof);
+    }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma clang loop unroll(full)
+  for (int k = 0; k < NS; k += 2) {
+    last_step(f0, f1, ke - NS + k);
+    last_step(f1, f0, ke - NS + k + 1);
+  }
+  __syncthreads();
+
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < M; ++mi)
+#pragma clang loop unroll(full)
+    for (int ni = 0; ni < M; ++ni)
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 16; ++e)
+        lds[(wm * 96 + mi * 32 + 8 * (e / 4) + 4 * h + e % 4) * S + wn * 96 + ni * 32 + r] =
+            acc[mi][ni][e];
+  __syncthreads();
+  const float as = alpha * ep.oscale, oc = (ep.centring & kCentredOut) ? kPlaneCentre : 0.0f;
+  const int nv = ep.n_valid;
+  double t1 = 0.0, t2 = 0.0;
+  float* img = lds + er * S + ec;
+  const int64_t oof = int64_t(er) * ep.ld_out + ec;
+#pragma clang loop unroll(full)
+  for (int i = 0; i < T / 16; ++i)
+#pragma clang loop unroll(full)
+    for (int j = 0; j < 3; ++j) {
+      const int row0 = R0 + 16 * i, col0 = C0 + 64 * j;
+      float* m = img + 16 * i * S + 64 * j;
+      f32x4 v = *reinterpret_cast<const f32x4*>(m);
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 4; ++e) v[e] = use_c ? fmaf(as, v[e], beta * c[i][j][e]) : as * v[e];
+      if (row0 >= np || col0 >= np) v = f32x4{0.0f, 0.0f, 0.0f, 0.0f};   // other rows' products
+      *reinterpret_cast<f32x4*>(m) = v;
+      if (diag && 64 * j + ec <= 16 * i + er) continue;   // left to the next pass
+#pragma clang loop unroll(full)
+      for (int e = 0; e < 4; ++e) {
+        const double d = static_cast<double>(v[e]);
+        t2 += d * d;   // doubled in tile_finish
+      }
+      if (ep.out && ep.vec_ok && row0 + 16 <= nv && col0 + 64 <= nv)
+        *reinterpret_cast<f32x4*>(ep.out + int64_t(row0) * ep.ld_out + col0 + oof) = v;
+    }
+  if (ep.out && !(ep.vec_ok && R0 + T <= nv && C0 + T <= nv)) {
+    // blocks that end past the result, or all of an unaligned one
+#pragma clang loop unroll(disable)
+    for (int b = 0; b < T / 16 * 3; ++b) {
+      const int row0 = R0 + b / 3 * 16, col0 = C0 + b % 3 * 64;
+      if (ep.vec_ok && row0 + 16 <= nv && col0 + 64 <= nv) continue;
+      if (diag && col0 + ec <= row0 + er) continue;
+#pragma clang loop unroll(disable)
+      for (int e = 0; e < 4; ++e)
+        if (row0 + er < nv && col0 + ec + e < nv)
+          ep.out[int64_t(row0) * ep.ld_out + col0 + oof + e] = img[b / 3 * 16 * S + b % 3 * 64 + e];
+    }
+  }
+  __syncthreads();
+  if (diag) {
+    // The groups above the diagonal are mirrored in the image; those on it
+    // finish their upper elements.
+#pragma clang loop unroll_count(2)
+    for (int g = threadIdx.x; g < T * T / 4; g += 256) {
+      const int rl = g % T, cl = g / T * 4;   // consecutive rows: no bank conflicts
+      if (cl > rl) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + rl * S + cl);
+#pragma clang loop unroll(full)
+        for (int e = 0; e < 4; ++e) lds[(cl + e) * S + rl] = v[e];
+      } else if (cl + 3 >= rl) {
+#pragma clang loop unroll(disable)
+        for (int e = rl - cl; e < 4; ++e) {
+          const int row = R0 + rl, col = C0 + cl + e;
+          float x = lds[rl * S + cl + e];
+          const bool on = col == row, real_on = on && col < ep.n_diag;
+          if (real_on) x += gamma;
+          lds[(cl + e) * S + rl] = real_on ? x - oc : x;
+          const double d = static_cast<double>(x);
+          t1 += on ? d : 0.0;
+          t2 += (on ? 0.5 : 1.0) * d * d;
+          if (ep.out && col < nv) ep.out[int64_t(row) * ep.ld_out + col] = x;
+        }
+      }
+    }
+    __syncthreads();
+  }
+  tile_finish<KIND, T, 1, S>(ep, R0, C0, w, lane, lds, red, tile, t1, t2);
 }
 
 // ---------------------------------------------------------------------------

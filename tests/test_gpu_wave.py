@@ -1,5 +1,5 @@
-"""k_sym_wave and k_wave_f32 (the products of small orders) at the edges of
-their tile sizes: one layer against the FP64 product of the operands it
+"""k_sym_wave, k_wave_f32 and k_sym_mid (the products of small orders) at the
+edges of their tile sizes: one layer against the FP64 product of the operands it
 multiplies, two layers inside a solve, whose recorded traces must be those
 of the returned iterate, and the two- and four-segment FP32 products of the
 derivatives."""
@@ -190,3 +190,15 @@ def test_split_pair_of_96_row_tiles(pk, n):
     ref = o @ c @ w.T.contiguous()
     ref = ref + ref.T
     assert ((p1.double() - ref).norm() / ref.norm()).item() <= 25 * 30 * 2.0 ** -17
+
+
+@pytest.mark.parametrize("n", [3841, 4033, 4095, 4096, 4097])
+def test_192_row_tiles(pk, n):
+    """The first and last orders of the 192-row tiles (k_sym_mid), whose last
+    row of tiles ends past the padded order, and the order after them."""
+    test_layer_at_tile_edges(pk, n)
+    test_traces_are_those_of_the_iterate(pk, n)
+
+
+def test_split_pair_of_192_row_tiles(pk):
+    test_split_pair_of_96_row_tiles(pk, 4095)
