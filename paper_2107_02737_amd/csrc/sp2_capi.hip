@@ -3,9 +3,8 @@
 // One solve: Gershgorin bounds -> input layer (fused split + trace
 // partials) -> layer loop -> optional McWeeny refinement -> P.  Every layer
 // launch decides its own branch and stop from the FP64 trace partials left
-// by the previous launch, so the host never waits between layers; it polls
-// the device stop flag once per chunk of layers while the next chunk is
-// already queued.
+// by the previous launch, so the host never waits between layers; it follows
+// the launches' progress in a pinned word with a few of them queued ahead.
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -14,6 +13,7 @@
 #include <cmath>
 #include <atomic>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "sp2_aux.hpp"
@@ -64,9 +64,15 @@ sp2_status fail(sp2_status s, const char* fmt, ...) {
 
 constexpr int64_t kPad = 256;          // matrices are padded to a multiple of this
 constexpr int kBand = 4;               // tile-rows per band of the tile schedule
-// Layers launched between stop-flag polls: 8, or 2 once a layer is long
-// (np >= 4096: ~0.5 ms and more), so that few launches run after the stop
-// while the queued chunk still covers the host's poll.
+// Launches of the layer loop queued or running, as the host sees it in the mail
+// word of the solve: the running one and the next keep the device busy (a layer
+// takes 6 us at the least, a launch 2 and the word's way back about 2), and
+// little runs after the stop (a launch that exits costs 4 to 8 us).  Polling a
+// copy of the control block, a chunk of 8 layers behind the queue, left up to 15
+// such launches and a copy per chunk.  Solve of n = 256 271 us that way, 207 with
+// 2 launches, 222 with 3, 218 with 6; n = 402 344, 304 with 3, 4% less with 2; n =
+// 1026 532, 482, 485, 495.  Without pinned memory: a synchronisation per chunk.
+constexpr int kAhead = 2;
 constexpr int kChunk = 8;
 constexpr int kChunkLarge = 2;
 constexpr int64_t kChunkLargeNp = 4096;
@@ -328,20 +334,25 @@ float out_scale_of(int precision) {
 
 // Pinned host mirror of the control block and history, one per thread.
 struct HostMirror {
-  Ctrl ctrl[2];
+  Ctrl ctrl[1];
   Hist hist;
   Meta meta;
   XlState xl;
   int xl_stop;
   double ritz[4];
+  uint64_t mail;      // written by the layer launches of the solve `token`
+  uint32_t token;
 };
 thread_local HostMirror* g_host = nullptr;
 
 sp2_status host_mirror(HostMirror** out) {
   if (!g_host) {
     void* p = nullptr;
-    HIP_TRY(hipHostMalloc(&p, sizeof(HostMirror), hipHostMallocDefault));
+    // coherent and mapped on every device: kernels write the mail word
+    HIP_TRY(hipHostMalloc(&p, sizeof(HostMirror),
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
     g_host = static_cast<HostMirror*>(p);
+    memset(p, 0, sizeof(HostMirror));
   }
   *out = g_host;
   return SP2_OK;
@@ -670,8 +681,11 @@ float* s_f32(const WS& w, int precision, int n) {
 // the recorded layer.  src/dst FP32 buffers may alias (split modes only).
 sp2_status launch_layer(const WS& w, int precision, int n, int mode, const float* src, float* dst,
                         int pair_in, int pair_out, double* parts_out, hipStream_t st,
-                        const sp2_options* o, int64_t n_occ, bool full_out = true) {
+                        const sp2_options* o, int64_t n_occ, bool full_out = true,
+                        uint64_t* mail = nullptr, uint32_t token = 0) {
   Decide d = make_decide(w, mode, n);
+  d.mail = mail;
+  d.token = token;
   if (mode == 1) {
     d.parts_in = w.parts[n & 1];
     d.nparts_in = nparts_of_layer(w, precision, n);
@@ -743,12 +757,10 @@ __global__ void k_drop_tape(Meta* m) { m->valid = 0; }
 // Events of this thread on the current device, created on first use and
 // kept until the process ends (a solve records into them; creating and
 // destroying hundreds of events per solve would cost more than the
-// records).  Timing events for SP2_FLAG_TIME_LAYERS; two untimed events for
-// the stop-flag polls.
+// records): the timing events of SP2_FLAG_TIME_LAYERS.
 struct EventPool {
   int dev = -1;
   std::vector<hipEvent_t> timed;
-  hipEvent_t poll[2] = {nullptr, nullptr};
 };
 
 hipError_t event_pool(EventPool** out, size_t timed) {
@@ -758,10 +770,6 @@ hipError_t event_pool(EventPool** out, size_t timed) {
   if (r != hipSuccess) return r;
   if (dev < 0 || dev >= 16) return hipErrorInvalidDevice;
   EventPool& p = pools[dev];
-  if (!p.poll[0]) {
-    for (auto& e : p.poll)
-      if ((r = hipEventCreateWithFlags(&e, hipEventDisableTiming)) != hipSuccess) return r;
-  }
   while (p.timed.size() < timed) {
     hipEvent_t e = nullptr;
     if ((r = hipEventCreate(&e)) != hipSuccess) return r;
@@ -971,10 +979,47 @@ sp2_status noalloc_scratch(void** out) {
   return SP2_OK;
 }
 
+// Wait until the mail word of solve `token` shows the stop or a layer of at least
+// `layer`; the word's state (0: not stopped) goes to *state.  The stream is
+// queried now and then: a fault on it ends the wait, and on a drained stream
+// whose word is another's (a call that failed before left launches behind) the
+// control block is read instead.
+sp2_status await_layer(const WS& w, HostMirror* hm, uint32_t token, int layer, hipStream_t st,
+                       uint64_t* state) {
+  *state = 0;
+  for (uint32_t spin = 1;; ++spin) {
+    const uint64_t m = __atomic_load_n(&hm->mail, __ATOMIC_ACQUIRE);
+    if (m >> 48 == token) {
+      if (m & kMailStopped) {
+        *state = m;
+        return SP2_OK;
+      }
+      if (static_cast<int>(m & 0xffff) > layer) return SP2_OK;
+    }
+    if (spin % 4096 == 0) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipSuccess && __atomic_load_n(&hm->mail, __ATOMIC_ACQUIRE) == m) {
+        if (sp2_status s = read_back(w, hm, false, st)) return s;
+        const Ctrl& c = hm->ctrl[0];
+        if (c.stopped)
+          *state = kMailStopped | (c.converged ? kMailConverged : 0) |
+                   (c.acc_failed ? kMailAccFailed : 0) | (c.nonfinite ? kMailNonfinite : 0) |
+                   (c.degenerate ? kMailDegenerate : 0) | uint64_t(c.n_iter) << 32;
+        return SP2_OK;
+      }
+      if (e != hipSuccess && e != hipErrorNotReady)
+        return fail(SP2_ERR_DEVICE, "poll: %s", hipGetErrorString(e));
+      (void)hipGetLastError();   // not-ready is no error of the next launch
+      std::this_thread::yield();
+    }
+    __builtin_ia32_pause();
+  }
+}
+
 // One solve on a bound workspace.  `pinned`: hm is pinned host memory, and
-// the layer loop polls the stop flag of chunk c asynchronously (events)
-// while chunk c+1 runs; otherwise (plain host memory) it synchronises the
-// stream after every chunk.
+// the layer loop follows the stop flag in its mail word with kAhead launches
+// queued; otherwise (plain host memory) it synchronises the stream after every
+// chunk.
 sp2_status density_impl(const float* H, int64_t n, int64_t ld, int64_t n_occ, const sp2_options& o,
                         const Layout& L, float* P, sp2_info* info, uint8_t* branches,
                         int32_t branches_cap, void* workspace, hipStream_t st, HostMirror* hm,
@@ -1037,26 +1082,28 @@ sp2_status density_impl(const float* H, int64_t n, int64_t ld, int64_t n_occ, co
   if (o.flags & SP2_FLAG_TIME_LAYERS) HIP_TRY(timer.init(o.max_iter));
   const int refine_ev = o.max_iter;   // event pair index of the refinement
 
-  // Layer loop in chunks; poll the stop flag of chunk c while chunk c+1 runs.
-  hipEvent_t* ev = nullptr;
+  // Layer loop.  The token tells this solve's mail from that of an earlier call
+  // of the thread that failed with launches still queued.
+  uint32_t token = 0;
   if (pinned) {
-    EventPool* pool = nullptr;
-    HIP_TRY(event_pool(&pool, 0));
-    ev = pool->poll;
+    token = hm->token = (hm->token + 1) & 0xffff;
+    __atomic_store_n(&hm->mail, uint64_t(token) << 48, __ATOMIC_RELEASE);
   }
-  int launched = 0, chunk = 0;
+  int launched = 0;
   bool stopped = false;
-  int stop_slot = -1;   // host copy of the control block that showed the stop
+  Ctrl cl;
+  memset(&cl, 0, sizeof(cl));
   sp2_status err = SP2_OK;
   while (!stopped && launched < o.max_iter && err == SP2_OK) {
-    const int end = std::min(o.max_iter, launched + (L.np >= kChunkLargeNp ? kChunkLarge : kChunk));
+    const int end = pinned ? launched + 1
+                           : std::min(o.max_iter, launched + (L.np >= kChunkLargeNp ? kChunkLarge : kChunk));
     for (int k = launched; k < end && err == SP2_OK; ++k) {
       const float* src = s_f32(w, prec, k);
       float* dst = s_f32(w, prec, k + 1);
       if (timer.mark(2 * k, st) != hipSuccess) err = fail(SP2_ERR_DEVICE, "event record failed");
       if (err == SP2_OK)
         err = launch_layer(w, prec, k, 1, src, dst, k & 1, (k + 1) & 1, w.parts[(k + 1) & 1], st, &o,
-                           n_occ, prec == SP2_FP32);
+                           n_occ, prec == SP2_FP32, pinned ? &hm->mail : nullptr, token);
       if (err == SP2_OK && timer.mark(2 * k + 1, st) != hipSuccess)
         err = fail(SP2_ERR_DEVICE, "event record failed");
       if (err == SP2_OK && o.checkpoint_every > 0 && (k + 1) % o.checkpoint_every == 0) {
@@ -1071,41 +1118,35 @@ sp2_status density_impl(const float* H, int64_t n, int64_t ld, int64_t n_occ, co
     }
     launched = end;
     if (err != SP2_OK) break;
-    const int slot = chunk & 1;
-    hipError_t e = hipMemcpyAsync(&hm->ctrl[slot], w.ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, st);
     if (!pinned) {
-      if (e == hipSuccess) e = hipStreamSynchronize(st);
-      if (e != hipSuccess) { err = fail(SP2_ERR_DEVICE, "poll: %s", hipGetErrorString(e)); break; }
-      if (hm->ctrl[slot].stopped) {
+      err = read_back(w, hm, false, st);
+      if (err == SP2_OK && hm->ctrl[0].stopped) {
         stopped = true;
-        stop_slot = slot;
+        cl = hm->ctrl[0];
       }
-      ++chunk;
-      continue;
-    }
-    if (e == hipSuccess) e = hipEventRecord(ev[slot], st);
-    if (e != hipSuccess) { err = fail(SP2_ERR_DEVICE, "poll: %s", hipGetErrorString(e)); break; }
-    if (chunk > 0) {
-      e = hipEventSynchronize(ev[slot ^ 1]);
-      if (e != hipSuccess) { err = fail(SP2_ERR_DEVICE, "poll sync: %s", hipGetErrorString(e)); break; }
-      if (hm->ctrl[slot ^ 1].stopped) {
+    } else if (launched >= kAhead) {
+      uint64_t m = 0;
+      err = await_layer(w, hm, token, launched - kAhead, st, &m);
+      if (m & kMailStopped) {
         stopped = true;
-        stop_slot = slot ^ 1;
+        cl.stopped = 1;
+        cl.n_iter = static_cast<int32_t>(m >> 32 & 0xffff);
+        cl.converged = (m & kMailConverged) != 0;
+        cl.acc_failed = (m & kMailAccFailed) != 0;
+        cl.nonfinite = (m & kMailNonfinite) != 0;
+        cl.degenerate = (m & kMailDegenerate) != 0;
       }
     }
-    ++chunk;
   }
   if (err != SP2_OK) return err;
   // Once the stop flag is set the control block no longer changes (later
-  // layer launches exit at entry), so the host copy that showed it is final
+  // layer launches exit at entry), so the word or copy that showed it is final
   // and the rest of the solve is queued behind those launches without
-  // waiting.  (A copy of the last chunk may still be landing in the other
-  // host slot.)  At the layer cap: the freshest copy after the queue drains.
+  // waiting.  At the layer cap: a copy after the queue drains.
   if (!stopped) {
     if ((s = read_back(w, hm, false, st))) return s;
-    stop_slot = 0;
+    cl = hm->ctrl[0];
   }
-  const Ctrl cl = hm->ctrl[stop_slot];
   if (cl.nonfinite) {
     HIP_TRY(hipStreamSynchronize(st));   // nothing of this call lands after it returns
     return fail(SP2_ERR_NONFINITE, "H holds NaN or Inf");

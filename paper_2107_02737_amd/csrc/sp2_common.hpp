@@ -88,7 +88,31 @@ struct Decide {
   double n_occ, tol, stall_gate;
   int stop_rule;
   int quiet;                // 1: decide without recording (a second kernel of the same layer)
+  uint64_t* mail;           // pinned host word that follows the solve (null: none)
+  uint32_t token;           // the solve, in its top 16 bits
 };
+
+// What a layer launch tells the host, in one 64-bit store to pinned memory: the
+// solve's token, the layers applied when the network stopped, the state, and
+// the launch's layer + 1 -- so the host follows the stop flag without a copy or
+// an event on the stream.
+constexpr uint64_t kMailStopped = 1u << 16, kMailConverged = 1u << 17, kMailAccFailed = 1u << 18,
+                   kMailNonfinite = 1u << 19, kMailDegenerate = 1u << 20;
+__device__ __forceinline__ void post_mail(const Decide& d, uint64_t state, int n_iter) {
+  if (d.mail)
+    __hip_atomic_store(d.mail,
+                       uint64_t(d.token) << 48 | uint64_t(n_iter) << 32 | state | uint64_t(d.layer + 1),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same from a launch that found the flag set (one thread of it).
+__device__ __forceinline__ void post_stopped(const Decide& d) {
+  if (d.quiet || blockIdx.x != 0 || threadIdx.x != 0) return;
+  const Ctrl& c = *d.ctrl;
+  post_mail(d, kMailStopped | (c.converged ? kMailConverged : 0) | (c.acc_failed ? kMailAccFailed : 0) |
+                   (c.nonfinite ? kMailNonfinite : 0) | (c.degenerate ? kMailDegenerate : 0),
+            c.n_iter);
+}
 
 // ---------------------------------------------------------------------------
 // Reductions (fixed order, so every work-group and every run agrees bitwise)
@@ -224,12 +248,14 @@ __device__ __forceinline__ LayerCoef decide_from_sums(const Decide& d, double t1
       d.ctrl->converged = stop ? 1 : 0;
       d.ctrl->acc_failed = failed ? 1 : 0;
       __atomic_store_n(&d.ctrl->stopped, 1, __ATOMIC_RELAXED);
+      post_mail(d, kMailStopped | (stop ? kMailConverged : 0) | (failed ? kMailAccFailed : 0), n);
     } else if (!scheduled) {
       d.hist->branch[n] = sign;
       d.hist->coef[n][0] = sign > 0 ? 1.0 : -1.0;
       d.hist->coef[n][1] = sign > 0 ? 0.0 : 2.0;
       d.hist->coef[n][2] = 0.0;
     }
+    if (!(stop || failed)) post_mail(d, 0, 0);
   }
   if (stop || failed) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
   return scheduled ? sched : plain_coef(sign);
@@ -245,7 +271,10 @@ __device__ __forceinline__ LayerCoef decide_layer(const Decide& d, double* red) 
   __shared__ int s_stopped;
   if (threadIdx.x == 0) s_stopped = __atomic_load_n(&d.ctrl->stopped, __ATOMIC_RELAXED);
   __syncthreads();
-  if (s_stopped) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  if (s_stopped) {
+    post_stopped(d);
+    return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  }
   double t1 = 0.0, t2 = 0.0;
   for (int i = threadIdx.x; i < d.nparts_in; i += NT) {
     t1 += d.parts_in[2 * i];

@@ -90,7 +90,10 @@ __device__ __forceinline__ LayerCoef decide_layer_wave(const Decide& d) {
   }
   t1 = wave_total(t1);
   t2 = wave_total(t2);
-  if (__builtin_amdgcn_readfirstlane(stopped)) return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  if (__builtin_amdgcn_readfirstlane(stopped)) {
+    post_stopped(d);
+    return LayerCoef{0, 0.0f, 0.0f, 0.0f};
+  }
   return decide_from_sums(d, t1, t2, acc_len, stall_from, ep, hc);
 }
 
