@@ -173,8 +173,36 @@ __device__ __forceinline__ void tile_planes(const float* tile, int64_t R0, int64
       lv[e] = uint32_t(l8[2 * e]) | (uint32_t(l8[2 * e + 1]) << 16);
     }
     *reinterpret_cast<u32x4*>(hi + o) = hv;
-    *reinterpret_cast<u32x4*>(lo + o) = lv;
+    if (lo) *reinterpret_cast<u32x4*>(lo + o) = lv;
   }
+}
+
+// Rows i0, i0 + 4, ... of a 32 x 256 tile, columns j0 .. j0 + 3 (zero past n),
+// every load issued before the first use (two rows at a time, between the stores
+// of the ones before, a load waited for those); past the matrix a lane reads an
+// entry of it again, so that no load hangs on a branch.
+__device__ __forceinline__ void load_rows(f32x4 (&v)[kInRows / 4], const float* __restrict__ X, int64_t n,
+                                          int64_t ld, bool vec, int64_t i0, int64_t j0, bool inside) {
+  if (vec && (inside || n % 4 == 0)) {
+    const bool in = j0 < n;
+#pragma unroll
+    for (int k = 0; k < kInRows / 4; ++k)
+      v[k] = *reinterpret_cast<const f32x4*>(X + min(i0 + 4 * k, n - 1) * ld + (in ? j0 : 0));
+    if (inside) return;
+#pragma unroll
+    for (int k = 0; k < kInRows / 4; ++k)
+      if (!in || i0 + 4 * k >= n) v[k] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < kInRows / 4; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[k][c] = X[min(i0 + 4 * k, n - 1) * ld + min(j0 + c, n - 1)];
+#pragma unroll
+  for (int k = 0; k < kInRows / 4; ++k)
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+      if (i0 + 4 * k >= n || j0 + c >= n) v[k][c] = 0.0f;
 }
 
 __global__ __launch_bounds__(kEwThreads) void k_input_layer(const float* __restrict__ H, int64_t n,
@@ -198,21 +226,12 @@ __global__ __launch_bounds__(kEwThreads) void k_input_layer(const float* __restr
   for (int64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
     const int64_t R0 = (tl / tiles_c) * kInRows, C0 = (tl % tiles_c) * kInCols;
     const int64_t j0 = C0 + 4 * q;
-#pragma unroll 2
+    f32x4 h[kInRows / 4];
+    load_rows(h, H, n, ld, vec, R0 + rsub, j0, R0 + kInRows <= n && C0 + kInCols <= n);
+#pragma unroll
     for (int k = 0; k < kInRows / 4; ++k) {
       const int r = rsub + 4 * k;
       const int64_t i = R0 + r;
-      float h4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (i < n) {
-        if (vec && j0 + 3 < n) {
-          const f32x4 h = *reinterpret_cast<const f32x4*>(H + i * ld + j0);
-          h4[0] = h[0]; h4[1] = h[1]; h4[2] = h[2]; h4[3] = h[3];
-        } else {
-#pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (j0 + c < n) h4[c] = H[i * ld + j0 + c];
-        }
-      }
       float v[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -222,7 +241,7 @@ __global__ __launch_bounds__(kEwThreads) void k_input_layer(const float* __restr
           if (degenerate)
             x = (i == j) ? 0.5f : 0.0f;
           else
-            x = static_cast<float>(((i == j ? emax : 0.0) - static_cast<double>(h4[c])) * inv);
+            x = static_cast<float>(((i == j ? emax : 0.0) - static_cast<double>(h[k][c])) * inv);
         }
         v[c] = x;
         const double xd = static_cast<double>(x);
@@ -278,9 +297,14 @@ __global__ __launch_bounds__(kEwThreads) void k_split(const float* __restrict__ 
 // real ones of a padded matrix) into the K-tiled hi/lo planes of an np x np
 // matrix (np a multiple of 256; rows and columns in [n, np) are zero):
 // work-groups stride over 32 x 256 tiles, read a row at a time and written
-// as planes from LDS (tile_planes).
+// as planes from LDS (tile_planes; no lo plane if lo is null, no planes if split
+// is 0).  With `out`, X itself goes there padded to np x np, so that a layer call
+// reads its operand once, in one launch: with the loads ahead (load_rows) a call
+// of n = 1000 (FP16X3) takes 34.8 us instead of 39.1, one of n = 3072 (BF16X1)
+// 97 instead of 112.6, of which 17.8 here (113 MB, 6.4 TB/s).
 __global__ __launch_bounds__(kEwThreads) void k_split_tiled(const float* __restrict__ X, int64_t n,
                                                             int64_t ld, int64_t np,
+                                                            float* __restrict__ out,
                                                             uint16_t* __restrict__ hi,
                                                             uint16_t* __restrict__ lo, int split,
                                                             float centre, int64_t nd) {
@@ -291,25 +315,19 @@ __global__ __launch_bounds__(kEwThreads) void k_split_tiled(const float* __restr
   for (int64_t tl = blockIdx.x; tl < ntiles; tl += gridDim.x) {
     const int64_t R0 = (tl / tiles_c) * kInRows, C0 = (tl % tiles_c) * kInCols;
     const int64_t j0 = C0 + 4 * q;
-#pragma unroll 2
+    f32x4 v[kInRows / 4];
+    load_rows(v, X, n, ld, vec, R0 + rsub, j0, R0 + kInRows <= n && C0 + kInCols <= n);
+#pragma unroll
     for (int k = 0; k < kInRows / 4; ++k) {
       const int r = rsub + 4 * k;
       const int64_t i = R0 + r;
-      f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (i < n) {
-        if (vec && j0 + 3 < n) {
-          v = *reinterpret_cast<const f32x4*>(X + i * ld + j0);
-        } else {
+      if (out) *reinterpret_cast<f32x4*>(out + i * np + j0) = v[k];
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            if (j0 + c < n) v[c] = X[i * ld + j0 + c];
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          if (i == j0 + c && i < nd) v[c] -= centre;
-      }
-      *reinterpret_cast<f32x4*>(tile + r * kInLd + 4 * q) = v;
+      for (int c = 0; c < 4; ++c)
+        if (i == j0 + c && i < nd) v[k][c] -= centre;
+      if (split) *reinterpret_cast<f32x4*>(tile + r * kInLd + 4 * q) = v[k];
     }
+    if (!split) continue;
     __syncthreads();
     tile_planes(tile, R0, C0, np, split, hi, lo);
     __syncthreads();   // the next tile reuses the LDS

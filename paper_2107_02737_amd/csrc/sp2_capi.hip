@@ -836,7 +836,7 @@ sp2_status refine(const WS& w, int precision, int refine_mode, int n_iter, const
   constexpr float c = kPlaneCentre;
   const int p = precision == SP2_FP32 ? 0 : (n_iter & 1);
   if (precision != SP2_FP16X3) {
-    k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(S, L.np, L.np, L.np, w.hi(p), w.lo(p), 2,
+    k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(S, L.np, L.np, L.np, nullptr, w.hi(p), w.lo(p), 2,
                                                         c, L.n);
     LAUNCH_TRY();
   }
@@ -1463,7 +1463,11 @@ sp2_status sp2_layer(const float* X, int64_t n, int64_t ld, int32_t precision, i
   k_drop_tape<<<1, 1, 0, st>>>(w.meta);
   LAUNCH_TRY();
   float* Xp = w.slotf(0);
-  k_copy_scaled<<<ew_grid(L.np * L.np), kEwThreads, 0, st>>>(X, ld, Xp, L.np, n, L.np, 1.0f, 0);
+  // the padded operand and, as in the network, the planes of X - cI: X^2 =
+  // (X - cI)^2 + 2c X - c^2 I
+  k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(
+      X, n, ld, L.np, Xp, w.hi(0), precision == SP2_BF16X1 ? nullptr : w.lo(0),
+      precision == SP2_FP32 ? 0 : split_code_of(precision), kPlaneCentre, n);
   LAUNCH_TRY();
   Epi e = make_epi(L);
   e.c = Xp;
@@ -1479,10 +1483,6 @@ sp2_status sp2_layer(const float* X, int64_t n, int64_t ld, int32_t precision, i
     const float* A[1] = {Xp};
     s = launch_f32(w, 1, A, A, e, d0, st);
   } else {
-    // as in the network: the planes hold X - cI, X^2 = (X - cI)^2 + 2c X - c^2 I
-    k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(Xp, L.np, L.np, L.np, w.hi(0), w.lo(0),
-                                                        split_code_of(precision), kPlaneCentre, L.n);
-    LAUNCH_TRY();
     e.beta += 2.0f * kPlaneCentre * e.alpha;
     e.gamma = -kPlaneCentre * kPlaneCentre * e.alpha;
     e.n_diag = static_cast<int>(n);
@@ -1600,7 +1600,7 @@ sp2_status sym_pair_split(const WS& w, const uint16_t* xh, const uint16_t* xl, i
 
 // BF16X3 planes of an FP32 derivative iterate (np x np) into pair `op`.
 sp2_status split_derivative(const WS& w, const float* X, int op, hipStream_t st) {
-  k_split_tiled<<<w.L.init_blocks, kEwThreads, 0, st>>>(X, w.L.np, w.L.np, w.L.np, dhi(w, op),
+  k_split_tiled<<<w.L.init_blocks, kEwThreads, 0, st>>>(X, w.L.np, w.L.np, w.L.np, nullptr, dhi(w, op),
                                                         dlo(w, op), split_code_of(SP2_BF16X3), 0.0f,
                                                         0);
   LAUNCH_TRY();
@@ -1699,7 +1699,7 @@ sp2_status refine_derivative_split(const WS& w, int ps, int qd, const float* S32
 sp2_status load_checkpoint(const WS& w, int prec, int slot, float* dst, hipStream_t st) {
   HIP_TRY(hipMemcpyAsync(dst, w.tape(slot), w.L.slot_bytes, hipMemcpyDeviceToDevice, st));
   if (prec != SP2_FP32) {
-    k_split_tiled<<<w.L.init_blocks, kEwThreads, 0, st>>>(dst, w.L.np, w.L.np, w.L.np, w.hi(0),
+    k_split_tiled<<<w.L.init_blocks, kEwThreads, 0, st>>>(dst, w.L.np, w.L.np, w.L.np, nullptr, w.hi(0),
                                                           w.lo(0), split_code_of(prec), kPlaneCentre,
                                                           w.L.n);
     LAUNCH_TRY();
@@ -1834,7 +1834,7 @@ sp2_status sp2_vjp(void* workspace, size_t ws_bytes, const float* W, int64_t ld,
     for (int nn = e - 1; nn >= c; --nn) {
       if (sd) {
         // centred planes of S_nn into pair 0 (the recomputation has moved on)
-        k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(w.seg(nn - c), L.np, L.np, L.np, w.hi(0),
+        k_split_tiled<<<L.init_blocks, kEwThreads, 0, st>>>(w.seg(nn - c), L.np, L.np, L.np, nullptr, w.hi(0),
                                                             w.lo(0), split_code_of(SP2_BF16X3),
                                                             kPlaneCentre, L.n);
         LAUNCH_TRY();
