@@ -421,23 +421,26 @@ int wave_pieces(const Layout& L, int nseg) {
   return std::min(d.nsplit, kWaveMaxWaves);
 }
 
-// Tile rows (32 or 64) of the k_wave_f32 launches of this order, 0 where they
-// run on the 256 x 256 kernel: a launch of few tiles is bound by its latency,
-// so 32 rows while they make one round of the machine, 64 while they make two.
-// us per FP32 layer, k_wave_f32 / 256 x 256 kernel: n = 1026 50 / 79; n = 1984
-// 117 / 141.
+// Tile rows (32, 64 or 96) of the k_wave_f32 launches of this order, 0 where they
+// run on the 256 x 256 kernel: a launch of few tiles is bound by its latency, so
+// 32 rows while they make one round of the machine, 64 while they make one and a
+// half (their second round overlaps the first), 96 while they make one.  us per
+// FP32 layer, 64-row tiles / 96-row / 256 x 256 kernel: n = 1026 50 / - / 79; n =
+// 1536 71 / 84 / 90; n = 1984 117 / 102 / 141; n = 2046 - / 107 / 147.
 int wave_rows_f32(const Layout& L) {
   const int cus = device_cus();
-  const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64;
+  const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64, c = (L.np + 95) / 96;
   if (a * (a + 1) / 2 <= std::min(cus, L.max_parts)) return 32;
-  if (b * (b + 1) / 2 <= std::min(2 * cus, L.max_parts)) return 64;
+  if (b * (b + 1) / 2 <= std::min(cus + cus / 2, L.max_parts)) return 64;
+  if (c * (c + 1) / 2 <= std::min(cus, L.max_parts)) return 96;
   return 0;
 }
 
 // Tile rows (32, 64 or 96) of the k_sym_wave launches of this order, 0 where
-// they run on the 256 x 256 kernel: as above, and 96 rows in place of a second
-// or third round of 64 if they make one round and their eight waves (a 96-row
-// wave tile takes half the registers of a SIMD) can take a K piece each.  us
+// they run on the 256 x 256 kernel: 32 while they make one round, 64 while they
+// make two, but 96 in place of a second or third round of 64 if they make one
+// round and their eight waves (a 96-row wave tile takes half the registers of a
+// SIMD) can take a K piece each.  us
 // per FP16X3 layer, 32-row tiles / 64-row / 96-row / 256 x 256 kernel: n = 402
 // 8.6 / 11.2 / - / 25.8; n = 750 16.3 / 13.7 / 23.5 / 31; n = 1026 24 / 17.7 /
 // 25 / 35.6; n = 1536 - / 33 / 35 (12 pieces) / 46; n = 1980 - / 43.3 / 39.8 /
@@ -445,12 +448,13 @@ int wave_rows_f32(const Layout& L) {
 // It depends on the order alone: a launch over n rows leaves padding unwritten
 // that the 256 x 256 kernel would read.
 int wave_rows(const Layout& L) {
-  const int cus = device_cus(), rows = wave_rows_f32(L);
-  const int64_t b = (L.n + 63) / 64, c = (L.np + 95) / 96;
-  if (rows != 32 && b * (b + 1) / 2 > cus && c * (c + 1) / 2 <= std::min(cus, L.max_parts) &&
+  const int cus = device_cus();
+  const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64, c = (L.np + 95) / 96;
+  if (a * (a + 1) / 2 <= std::min(cus, L.max_parts)) return 32;
+  if (b * (b + 1) / 2 > cus && c * (c + 1) / 2 <= std::min(cus, L.max_parts) &&
       wave_pieces(L, 1) <= WaveShape<3>::kMaxWaves)
     return 96;
-  return rows;
+  return b * (b + 1) / 2 <= std::min(2 * cus, L.max_parts) ? 64 : 0;
 }
 
 // Wave launch covering the first `cover` rows, nseg K segments.
@@ -615,11 +619,13 @@ sp2_status launch_wave_f32(const WS& w, const F32Args& a, hipStream_t st) {
   v.epi = a.epi;
   v.dec = a.dec;
   v.g = wave_grid(w, wave_rows_f32(w.L), w.L.np, NSEG);
-  constexpr int threads = kWaveF32Waves * kWave;
-  if (wave_rows_f32(w.L) == 32)
-    k_wave_f32<1, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+  const int T = wave_rows_f32(w.L);
+  if (T == 32)
+    k_wave_f32<1, NSEG><<<v.g.ntiles, kWaveF32Waves<1> * kWave, 0, st>>>(v);
+  else if (T == 64)
+    k_wave_f32<2, NSEG><<<v.g.ntiles, kWaveF32Waves<2> * kWave, 0, st>>>(v);
   else
-    k_wave_f32<2, NSEG><<<v.g.ntiles, threads, 0, st>>>(v);
+    k_wave_f32<3, NSEG><<<v.g.ntiles, kWaveF32Waves<3> * kWave, 0, st>>>(v);
   LAUNCH_TRY();
   return SP2_OK;
 }

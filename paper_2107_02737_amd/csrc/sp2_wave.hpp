@@ -18,6 +18,8 @@
 // would be needed to go on.
 #pragma once
 
+#include <type_traits>
+
 #include "sp2_common.hpp"
 #include "sp2_gemm.hpp"
 
@@ -64,8 +66,9 @@ struct WaveShape {
   static constexpr int LD = T + 1, LP = 36;
   static constexpr int kMinWaves = MB < 3 ? 4 : 6, kMaxWaves = MB < 3 ? 12 : 8;
   static constexpr int kImg = (T * LD + 3) & ~3, kLds = kImg + kMaxWaves * T * LP;
-  static constexpr int Q = MB < 3 ? MB : 2;   // four-row groups per thread and strip
-  static_assert(Q * kMinWaves * kWave >= 8 * T, "a strip per pass");
+  // four-row groups of a strip per thread, of at least `waves` waves
+  static constexpr int groups(int waves) { return (8 * T + waves * kWave - 1) / (waves * kWave); }
+  static constexpr int Q = groups(kMinWaves);
 };
 constexpr int kWaveMaxWaves = 12;
 
@@ -126,13 +129,12 @@ __device__ __forceinline__ void wave_products(const WaveFrag<KIND, MB>& f, f32x1
 }
 
 // C of this thread: four rows of one column per group, strip mi of the tile.
-template <int MB>
-__device__ __forceinline__ void wave_load_c(f32x4 (&cv)[WaveShape<MB>::Q], const Epi& p, int R0,
-                                            int C0, int mi) {
+template <int MB, int Q>
+__device__ __forceinline__ void wave_load_c(f32x4 (&cv)[Q], const Epi& p, int R0, int C0, int mi) {
   constexpr int T = WaveShape<MB>::T;
   const int np = p.np, nt = blockDim.x;
 #pragma clang loop unroll(full)
-  for (int i = 0; i < WaveShape<MB>::Q; ++i) {
+  for (int i = 0; i < Q; ++i) {
     const int q = threadIdx.x + nt * i, col = C0 + q % T, row = R0 + 32 * mi + q / T * 4;
     const float* c = p.c + int64_t(row) * np + col;
     const bool in = p.c && q < 8 * T && (MB < 3 || (row < np && col < np));
@@ -232,14 +234,14 @@ __device__ __forceinline__ void tile_finish(const Epi& p, int R0, int C0, int w,
 // waits for every store issued before it.  The mirrored FP32 result and the
 // planes are written from the image.  The loops stay rolled: code that runs
 // once per work-group costs its instruction fetch, about a cycle per byte.
-template <int KIND, int MB>
+template <int KIND, int MB, int Q>
 __device__ __forceinline__ void wave_epilogue(const f32x16 (&acc)[MB][MB],
-                                              const f32x4 (&cs)[MB][WaveShape<MB>::Q], const Epi& p,
+                                              const f32x4 (&cs)[MB][Q], const Epi& p,
                                               float as, float beta, float gamma, int R0, int C0,
                                               int w, int nw, int lane, float* lds, double* red,
                                               int tile) {
   using Sh = WaveShape<MB>;
-  constexpr int T = Sh::T, S = Sh::LD, SP = Sh::LP, Q = Sh::Q;
+  constexpr int T = Sh::T, S = Sh::LD, SP = Sh::LP;
   const int np = p.np, nv = p.n_valid, NT = blockDim.x;
   const bool diag = R0 == C0, use_c = beta != 0.0f;
   const int t = threadIdx.x;
@@ -702,8 +704,8 @@ void k_sym_mid(WaveArgs p) {
 // eight times; the other five terms have an accumulator of their own, so their
 // sum (2^-8 of the main one) adds no rounding to it.
 //
-// Tiles and epilogue as in k_sym_wave; eight waves, each taking every eighth
-// pair of K steps.  Operands are row-major: a wave
+// Tiles and epilogue as in k_sym_wave; eight waves (four for 96-row tiles), each
+// taking every eighth pair of K steps.  Operands are row-major: a wave
 // copies its own blocks (32 rows x 16 values, 64 contiguous bytes per row) into
 // a private LDS ring with global_load_lds, NS - 1 steps ahead and without
 // barriers; lane (r, h) then reads its eight values of row r, two 16-byte
@@ -713,9 +715,10 @@ void k_sym_mid(WaveArgs p) {
 // for 6 MFMAs) or the MFMAs (64-row tiles).
 //
 // Against the FP32-MFMA kernel of 256 x 256 tiles and its split-K kernel: a
-// layer of n = 1026 50 us (79 before), n = 1536 71 (90), n = 1984 117 (141); an
-// FP32 solve of n = 256 382 us (1000).  Relative error of a layer of n = 1536
-// 1.7e-7 (2.1e-7 before), of an FP32 solve of n = 1026 3.9e-7 (5.5e-7).
+// layer of n = 1026 takes 50 us (79 before), n = 1536 71 (90), n = 2046 107
+// (147); an FP32 solve of n = 256 366 us (1000).  Relative error of a layer of n =
+// 1536 1.7e-7 (2.1e-7 before), n = 2046 2.4e-7 (3.3e-7), of an FP32 solve of n =
+// 1026 3.9e-7 (5.5e-7).
 // ---------------------------------------------------------------------------
 
 struct WaveF32Args {
@@ -726,7 +729,10 @@ struct WaveF32Args {
   WaveGrid g;
 };
 
-constexpr int kWaveF32Waves = 8;
+// Waves of a work-group: two per SIMD, one where a wave's two sets of
+// accumulators of 96 rows and two K steps take more than half the registers.
+template <int MB>
+constexpr int kWaveF32Waves = MB < 3 ? 8 : 4;
 
 // Three BF16 planes of eight FP32 values (an infinite one leaves NaN in m and
 // l: see add_cross).
@@ -756,10 +762,11 @@ __device__ __forceinline__ float add_cross(float acc, float crs) {
 }
 
 template <int MB, int NSEG>
-__global__ __launch_bounds__(kWaveF32Waves * kWave) __attribute__((amdgpu_waves_per_eu(2, 2)))
+__global__ __launch_bounds__(kWaveF32Waves<MB> * kWave)
+__attribute__((amdgpu_waves_per_eu(kWaveF32Waves<MB> / 4, kWaveF32Waves<MB> / 4)))
 void k_wave_f32(WaveF32Args p) {
   using Sh = WaveShape<MB>;
-  constexpr int NW = kWaveF32Waves, NS = MB == 1 ? 4 : 2;   // ring slots per wave
+  constexpr int NW = kWaveF32Waves<MB>, NS = MB == 1 ? 4 : 2;   // ring slots per wave
   constexpr int kSlot = MB * 2 * 2048;                      // bytes: A blocks, B blocks
   constexpr int kCopies = MB * 2 * 2;                       // 1 KB copies per step
   static_assert((Sh::kImg + NW * Sh::T * Sh::LP) * 4 <= NW * NS * kSlot, "epilogue fits the ring");
@@ -779,21 +786,15 @@ void k_wave_f32(WaveF32Args p) {
   // steps [0, qd) hold diagonal entries, [qd, qn) do not.
   constexpr int kTP = Sh::T / 32;
   const int kp = C0 < lim ? lim / 32 : 0;
-  const int sp = kp == 0 ? 0 : ti == tj ? kTP : 2 * kTP;
+  const int tc = min(kTP, kp - C0 / 32);   // a 96-row tile may end past lim
+  const int sp = kp == 0 ? 0 : ti == tj ? tc : kTP + tc;
   const int nd = NSEG * sp, nr = kp - sp;
   const int qn = (NSEG * kp - w + NW - 1) / NW * 2, qd = nd > w ? (nd - w + NW - 1) / NW * 2 : 0;
   // Copy i of a block: rows 16 i + lane / 4, 16-byte piece (lane % 4) of the
   // row's 64 bytes, which holds values 4 c .. 4 c + 3 with
   // c = (lane % 4) ^ (row / 2 % 4).
   const uint32_t src = ((lane & 3) ^ ((lane >> 3) & 3)) * 16;
-  uint32_t oa[MB][2], ob[MB][2];
-#pragma clang loop unroll(full)
-  for (int i = 0; i < MB; ++i)
-#pragma clang loop unroll(full)
-    for (int u = 0; u < 2; ++u) {
-      oa[i][u] = uint32_t(R0 + 32 * i + 16 * u + (lane >> 2)) * np * 4u + src;
-      ob[i][u] = uint32_t(C0 + 32 * i + 16 * u + (lane >> 2)) * np * 4u + src;
-    }
+  const uint32_t own = uint32_t(lane >> 2) * np * 4u + src;
   const uint32_t ring0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)(lds))) +
       w * (NS * kSlot);
@@ -805,7 +806,7 @@ void k_wave_f32(WaveF32Args p) {
     const int sg = (NSEG > 1 && x >= ns) + (NSEG > 2 && x >= 2 * ns) + (NSEG > 2 && x >= 3 * ns);
     x -= sg * ns;
     if (dg) {
-      x += x < kTP ? R0 / 32 : C0 / 32 - kTP;
+      x += ti == tj ? C0 / 32 : x < kTP ? R0 / 32 : C0 / 32 - kTP;
     } else {
       x += x >= R0 / 32 ? kTP : 0;
       x += ti != tj && x >= C0 / 32 ? kTP : 0;
@@ -815,12 +816,16 @@ void k_wave_f32(WaveF32Args p) {
     const float* gb = (sg == 0 ? p.b[0] : sg == 1 ? p.b[1] : sg == 2 ? p.b[2] : p.b[3]) + ko;
     const uint32_t m0s = ring0 + (slot & (NS - 1)) * kSlot;
 #pragma clang loop unroll(full)
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i) {
+      // (96-row tiles may end past np: those blocks take the last one's rows)
+      const float* ra = ga + int64_t(min(R0 + 32 * i, np - 32)) * np;
+      const float* rb = gb + int64_t(min(C0 + 32 * i, np - 32)) * np;
 #pragma clang loop unroll(full)
       for (int u = 0; u < 2; ++u) {
-        dma_chunk(oa[i][u], ga, m0s + i * 2048 + u * 1024);
-        dma_chunk(ob[i][u], gb, m0s + (MB + i) * 2048 + u * 1024);
+        dma_chunk(own, ra + u * 16 * int64_t(np), m0s + i * 2048 + u * 1024);
+        dma_chunk(own, rb + u * 16 * int64_t(np), m0s + (MB + i) * 2048 + u * 1024);
       }
+    }
   };
   if (qn > 0) {
 #pragma clang loop unroll(full)
@@ -833,6 +838,14 @@ void k_wave_f32(WaveF32Args p) {
     alpha = cf.a;
     beta = cf.b;
     gamma = cf.c;
+  }
+  if constexpr (MB > 2) {   // uniform, and no vector register is left for them
+    auto uniform = [](float x) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+    };
+    alpha = uniform(alpha);
+    beta = uniform(beta);
+    gamma = uniform(gamma);
   }
   f32x16 acc[MB][MB], crs[MB][MB];
 #pragma clang loop unroll(full)
@@ -848,20 +861,6 @@ void k_wave_f32(WaveF32Args p) {
   wait_vmem_all();   // the decision's loads, and with them the first copies
   if (cf.sign == 0) return;
 
-  struct Planes {
-    u32x4 a[3][MB], b[3][MB];
-  };
-  auto convert = [&](Planes& f, int q) {   // step q from its slot
-    const char* sl = ring + (q & (NS - 1)) * kSlot;
-#pragma clang loop unroll(full)
-    for (int i = 0; i < MB; ++i) {
-      split3(*reinterpret_cast<const f32x4*>(sl + i * 2048 + f0),
-             *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1), f.a[0][i], f.a[1][i], f.a[2][i]);
-      split3(*reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0),
-             *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1), f.b[0][i], f.b[1][i],
-             f.b[2][i]);
-    }
-  };
   // The reads of slot q are done: it takes step q + NS (at the end the last step
   // again, which is not read, so that the count of copies in flight stays).
   // After it step q + 1 has arrived.
@@ -899,44 +898,111 @@ void k_wave_f32(WaveF32Args p) {
           acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[mi][e / 4][e % 4], xb[ni][e / 4][e % 4],
                                                              acc[mi][ni], 0, 0, 0);
   }
-  // Step q from cur while step q + 1 is split into nxt.
-  auto step = [&](const Planes& cur, Planes& nxt, int q) {
-    refill(q);
-    __builtin_amdgcn_sched_barrier(0);
-    convert(nxt, q + 1);
-    constexpr int ta[6] = {0, 0, 1, 1, 0, 2}, tb[6] = {0, 1, 0, 1, 2, 0};
+  constexpr int ta[6] = {0, 0, 1, 1, 0, 2}, tb[6] = {0, 1, 0, 1, 2, 0};   // hh hm mh mm hl lh
+  if constexpr (MB < 3) {
+    struct Planes {
+      u32x4 a[3][MB], b[3][MB];
+    };
+    auto convert = [&](Planes& f, int q) {   // step q from its slot
+      const char* sl = ring + (q & (NS - 1)) * kSlot;
 #pragma clang loop unroll(full)
-    for (int k = 0; k < 6; ++k)
+      for (int i = 0; i < MB; ++i) {
+        split3(*reinterpret_cast<const f32x4*>(sl + i * 2048 + f0),
+               *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1), f.a[0][i], f.a[1][i], f.a[2][i]);
+        split3(*reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0),
+               *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1), f.b[0][i], f.b[1][i],
+               f.b[2][i]);
+      }
+    };
+    // Step q from cur while step q + 1 is split into nxt.
+    auto step = [&](const Planes& cur, Planes& nxt, int q) {
+      refill(q);
+      __builtin_amdgcn_sched_barrier(0);
+      convert(nxt, q + 1);
 #pragma clang loop unroll(full)
-      for (int mi = 0; mi < MB; ++mi)
+      for (int k = 0; k < 6; ++k)
+#pragma clang loop unroll(full)
+        for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+          for (int ni = 0; ni < MB; ++ni)
+            mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], cur.a[ta[k]][mi],
+                                   cur.b[tb[k]][ni]);
+      // the reads first, then the conversions spread over the MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x100, 4 * MB, 0);
+#pragma clang loop unroll(full)
+      for (int k = 0; k < 6 * MB * MB; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, MB == 1 ? 16 : 8, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    Planes f0s, f1s;
+    if (qn > qd) convert(f0s, qd);
+    for (int q = qd; q < qn; q += 2) {
+      step(f0s, f1s, q);
+      step(f1s, f0s, q + 1);
+    }
+  } else {
+    // One wave per SIMD: a row of three blocks is multiplied while the next A
+    // block is split, the last row while the first A block and the B blocks of
+    // step q + 1 are (two steps' planes of both operands would not fit).
+    struct Tri {
+      u32x4 v[3];
+    };
+    auto split = [&](Tri& x, int q, int block) {   // A blocks, then B blocks
+      const char* sl = ring + (q & (NS - 1)) * kSlot + block * 2048;
+      split3(*reinterpret_cast<const f32x4*>(sl + f0), *reinterpret_cast<const f32x4*>(sl + f1), x.v[0],
+             x.v[1], x.v[2]);
+    };
+    auto row = [&](const Tri& a, const Tri (&b)[MB], int mi, auto last) {
+#pragma clang loop unroll(full)
+      for (int k = 0; k < 6; ++k)
 #pragma clang loop unroll(full)
         for (int ni = 0; ni < MB; ++ni)
-          mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], cur.a[ta[k]][mi],
-                                 cur.b[tb[k]][ni]);
-    // the reads first, then the conversions spread over the MFMAs
-    __builtin_amdgcn_sched_group_barrier(0x100, 4 * MB, 0);
+          mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], a.v[ta[k]], b[ni].v[tb[k]]);
+      constexpr int kBlocks = decltype(last)::value ? 1 + MB : 1;
+      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kBlocks, 0);
 #pragma clang loop unroll(full)
-    for (int k = 0; k < 6 * MB * MB; ++k) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, MB == 1 ? 16 : 8, 0);
+      for (int k = 0; k < 6 * MB; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, (40 * kBlocks + 6 * MB - 1) / (6 * MB), 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto step = [&](Tri& a, Tri& a2, Tri (&b)[MB], Tri (&nb)[MB], int q) {   // row 0 in a
+      split(a2, q, 1);
+      row(a, b, 0, std::false_type());
+      split(a, q, 2);
+      row(a2, b, 1, std::false_type());
+      refill(q);
+      __builtin_amdgcn_sched_barrier(0);
+      split(a2, q + 1, 0);
+#pragma clang loop unroll(full)
+      for (int i = 0; i < MB; ++i) split(nb[i], q + 1, MB + i);
+      row(a, b, 2, std::true_type());
+    };
+    Tri a0, a1, b0[MB], b1[MB];
+    if (qn > qd) {
+      split(a0, qd, 0);
+#pragma clang loop unroll(full)
+      for (int i = 0; i < MB; ++i) split(b0[i], qd, MB + i);
     }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  Planes f0s, f1s;
-  if (qn > qd) convert(f0s, qd);
-  for (int q = qd; q < qn; q += 2) {
-    step(f0s, f1s, q);
-    step(f1s, f0s, q + 1);
+#pragma clang loop unroll(disable)
+    for (int q = qd; q < qn; q += 2) {
+      step(a0, a1, b0, b1, q);
+      step(a1, a0, b1, b0, q + 1);
+    }
   }
-  f32x4 cs[MB][Sh::Q];
-#pragma clang loop unroll(full)
-  for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
 #pragma clang loop unroll(full)
   for (int mi = 0; mi < MB; ++mi)
 #pragma clang loop unroll(full)
     for (int ni = 0; ni < MB; ++ni)
 #pragma clang loop unroll(full)
       for (int q = 0; q < 16; ++q) acc[mi][ni][q] = add_cross(acc[mi][ni][q], crs[mi][ni][q]);
+  if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);   // no registers for C before
+  f32x4 cs[MB][Sh::groups(NW)];
+#pragma clang loop unroll(full)
+  for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
   wait_vmem_all();
   __syncthreads();   // the rings are free
   wave_epilogue<kF32, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, NW, lane, lds,

@@ -202,3 +202,12 @@ def test_192_row_tiles(pk, n):
 
 def test_split_pair_of_192_row_tiles(pk):
     test_split_pair_of_96_row_tiles(pk, 4095)
+
+
+@pytest.mark.parametrize("n", [1728, 1729, 1793, 2047, 2048, 2049])
+def test_fp32_96_row_tiles(pk, n):
+    """FP32 layers from the last order of 64-row tiles to the first past the
+    96-row ones, and the pair products of one."""
+    test_fp32_layer_at_tile_edges(pk, n)
+    if n == 2047:
+        test_fp32_pair_products(pk, n)
