@@ -423,15 +423,16 @@ int wave_pieces(const Layout& L, int nseg) {
 
 // Tile rows (32, 64 or 96) of the k_wave_f32 launches of this order, 0 where they
 // run on the 256 x 256 kernel: a launch of few tiles is bound by its latency, so
-// 32 rows while they make one round of the machine, 64 while they make one and a
-// half (their second round overlaps the first), 96 while they make one.  us per
-// FP32 layer, 64-row tiles / 96-row / 256 x 256 kernel: n = 1026 50 / - / 79; n =
-// 1536 71 / 84 / 90; n = 1984 117 / 102 / 141; n = 2046 - / 107 / 147.
+// 32 rows while they make one round of the machine (a work-group's LDS ring lets
+// one of them on a CU), 64 while they make two, 96 while they make one.  us per
+// FP32 product, 64-row tiles / 96-row: n = 1792 74.7 / 86.5, n = 2046 126 / 100; us
+// per FP32 layer, these tiles / 256 x 256 kernel: n = 1026 53 / 80, n = 1536 89 / 90,
+// n = 1792 96 / 116, n = 2046 120 / 145.
 int wave_rows_f32(const Layout& L) {
   const int cus = device_cus();
-  const int64_t a = (L.n + 31) / 32, b = (L.n + 63) / 64, c = (L.np + 95) / 96;
+  const int64_t a = (L.n + 31) / 32, b = L.np / 64, c = (L.np + 95) / 96;
   if (a * (a + 1) / 2 <= std::min(cus, L.max_parts)) return 32;
-  if (b * (b + 1) / 2 <= std::min(cus + cus / 2, L.max_parts)) return 64;
+  if (b * (b + 1) / 2 <= std::min(2 * cus, L.max_parts)) return 64;
   if (c * (c + 1) / 2 <= std::min(cus, L.max_parts)) return 96;
   return 0;
 }

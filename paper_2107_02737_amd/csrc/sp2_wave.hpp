@@ -694,31 +694,24 @@ void k_sym_mid(WaveArgs p) {
 }
 
 // ---------------------------------------------------------------------------
-// FP32 products of small orders, sum_s A_s B_s^T over up to four K segments,
-// on the BF16 matrix cores.  An FP32 value is the sum of three BF16 values
-// h + m + l (8 significant bits each, signed: 26 bits), so
-//   x y = hh + (hm + mh) + (mm + hl + lh) + ...
-// with the terms left out below 2^-26 |x y|, a quarter of the rounding of one
-// FP32 product.  Six 32x32x16 MFMAs (192 cycles) stand for eight FP32 32x32x2
-// ones (512), and the accumulator of hh is rounded once per 16 K instead of
-// eight times; the other five terms have an accumulator of their own, so their
-// sum (2^-8 of the main one) adds no rounding to it.
+// FP32 products of small orders, sum_s A_s B_s^T over up to four K segments
+// (row-major operands), on the FP32 matrix cores.  Tiles and epilogue as in
+// k_sym_wave; eight waves (four for 96-row tiles) take an equal share of the K
+// steps (16 values) each.  A wave copies its own blocks (32 rows x 16 values, 64
+// contiguous bytes per row) into a private LDS ring with global_load_lds, NS steps
+// ahead and without barriers; lane (r, h) reads its eight values of row r, two
+// 16-byte pieces at positions swizzled by the row so that eight consecutive rows
+// use all banks, half a step ahead into registers, and feeds value 8 h + e to MFMA e.
+// A sum is cut after two steps (eight in 96-row tiles): it is added to a second set
+// of accumulators and the next begins at zero, so that few roundings meet the
+// full size of a result.
 //
-// Tiles and epilogue as in k_sym_wave; eight waves (four for 96-row tiles), each
-// taking every eighth pair of K steps.  Operands are row-major: a wave
-// copies its own blocks (32 rows x 16 values, 64 contiguous bytes per row) into
-// a private LDS ring with global_load_lds, NS - 1 steps ahead and without
-// barriers; lane (r, h) then reads its eight values of row r, two 16-byte
-// pieces at positions swizzled by the row so that eight consecutive rows use
-// all banks, and splits them in registers while the other wave of its SIMD
-// multiplies.  The bound is the splitting (32-row tiles: 96 VALU instructions
-// for 6 MFMAs) or the MFMAs (64-row tiles).
-//
-// Against the FP32-MFMA kernel of 256 x 256 tiles and its split-K kernel: a
-// layer of n = 1026 takes 50 us (79 before), n = 1536 71 (90), n = 2046 107
-// (147); an FP32 solve of n = 256 366 us (1000).  Relative error of a layer of n =
-// 1536 1.7e-7 (2.1e-7 before), n = 2046 2.4e-7 (3.3e-7), of an FP32 solve of n =
-// 1026 3.9e-7 (5.5e-7).
+// Against the 256 x 256 tiles and their split-K kernel: a layer of n = 1026 takes 53
+// us (80), n = 1536 89 (90), n = 1792 96 (116), n = 2046 120 (145); an FP32 solve of n
+// = 256 345 us (1039).  Of the 28 us of the product at n = 1026, 18 are the K loop, at
+// 80% of the FP32 matrix-core rate, 10 the launch, the decision and the epilogue.
+// Relative error of a layer of n = 1536 1.2e-7 (2.2e-7), n = 2046 2.2e-7 (3.3e-7), of
+// an FP32 solve of n = 1026 3.4e-7 (5.5e-7).
 // ---------------------------------------------------------------------------
 
 struct WaveF32Args {
@@ -733,33 +726,9 @@ struct WaveF32Args {
 // accumulators of 96 rows and two K steps take more than half the registers.
 template <int MB>
 constexpr int kWaveF32Waves = MB < 3 ? 8 : 4;
-
-// Three BF16 planes of eight FP32 values (an infinite one leaves NaN in m and
-// l: see add_cross).
-__device__ __forceinline__ void split3(const f32x4& x0, const f32x4& x1, u32x4& h, u32x4& m, u32x4& l) {
-  typedef __attribute__((ext_vector_type(2))) float f32x2;
-  typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-#pragma clang loop unroll(full)
-  for (int e = 0; e < 4; ++e) {
-    const float a = e < 2 ? x0[2 * e] : x1[2 * e - 4], b = e < 2 ? x0[2 * e + 1] : x1[2 * e - 3];
-    const uint32_t hw = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
-    const float ra = a - __builtin_bit_cast(float, hw << 16);
-    const float rb = b - __builtin_bit_cast(float, hw & 0xffff0000u);
-    const uint32_t mw = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{ra, rb}), bf16x2));
-    const f32x2 t = {ra - __builtin_bit_cast(float, mw << 16),
-                     rb - __builtin_bit_cast(float, mw & 0xffff0000u)};
-    h[e] = hw;
-    m[e] = mw;
-    l[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(t, bf16x2));
-  }
-}
-
-// Main and cross sums together.  Where the main sum is not finite (an operand
-// was infinite or NaN, or the sum overflowed) it is the result: the high parts
-// have the signs and zeros of the values themselves.
-__device__ __forceinline__ float add_cross(float acc, float crs) {
-  return fabsf(acc) < INFINITY ? acc + crs : acc;
-}
+// K steps (16 values) summed in one set of accumulators.
+template <int MB>
+constexpr int kF32Cut = MB < 3 ? 2 : 8;   // (one wave per SIMD: nothing hides the additions)
 
 template <int MB, int NSEG>
 __global__ __launch_bounds__(kWaveF32Waves<MB> * kWave)
@@ -780,16 +749,10 @@ void k_wave_f32(WaveF32Args p) {
   tile_of(tile, p.g.nt, p.g.band, ti, tj);
   const int R0 = ti * Sh::T, C0 = tj * Sh::T;   // R0 <= C0
 
-  // The tile's K steps, in pairs of 32 values: kp of them in every segment, of
-  // which the sp that hold diagonal entries of the tile's rows or columns come
-  // first, those of all segments together.  Wave w takes pairs w, w + NW, ...:
-  // steps [0, qd) hold diagonal entries, [qd, qn) do not.
-  constexpr int kTP = Sh::T / 32;
-  const int kp = C0 < lim ? lim / 32 : 0;
-  const int tc = min(kTP, kp - C0 / 32);   // a 96-row tile may end past lim
-  const int sp = kp == 0 ? 0 : ti == tj ? tc : kTP + tc;
-  const int nd = NSEG * sp, nr = kp - sp;
-  const int qn = (NSEG * kp - w + NW - 1) / NW * 2, qd = nd > w ? (nd - w + NW - 1) / NW * 2 : 0;
+  // This wave's K steps [s0, s0 + qn) of those of all segments together (a column
+  // past lim: both operands' rows are zero).
+  const int ks = C0 < lim ? lim / 16 : 0;
+  const int s0 = NSEG * ks * w / NW, qn = NSEG * ks * (w + 1) / NW - s0;
   // Copy i of a block: rows 16 i + lane / 4, 16-byte piece (lane % 4) of the
   // row's 64 bytes, which holds values 4 c .. 4 c + 3 with
   // c = (lane % 4) ^ (row / 2 % 4).
@@ -798,39 +761,31 @@ void k_wave_f32(WaveF32Args p) {
   const uint32_t ring0 =
       static_cast<uint32_t>(reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) float*)(lds))) +
       w * (NS * kSlot);
-  auto copy = [&](int q, int slot) {   // step q into slot `slot` mod NS
-    int x = w + (q >> 1) * NW;
-    const bool dg = x < nd;
-    const int ns = dg ? sp : nr;
-    x -= dg ? 0 : nd;
-    const int sg = (NSEG > 1 && x >= ns) + (NSEG > 2 && x >= 2 * ns) + (NSEG > 2 && x >= 3 * ns);
-    x -= sg * ns;
-    if (dg) {
-      x += ti == tj ? C0 / 32 : x < kTP ? R0 / 32 : C0 / 32 - kTP;
-    } else {
-      x += x >= R0 / 32 ? kTP : 0;
-      x += ti != tj && x >= C0 / 32 ? kTP : 0;
-    }
-    const int64_t ko = x * 32 + (q & 1) * 16;
-    const float* ga = (sg == 0 ? p.a[0] : sg == 1 ? p.a[1] : sg == 2 ? p.a[2] : p.a[3]) + ko;
-    const float* gb = (sg == 0 ? p.b[0] : sg == 1 ? p.b[1] : sg == 2 ? p.b[2] : p.b[3]) + ko;
-    const uint32_t m0s = ring0 + (slot & (NS - 1)) * kSlot;
-#pragma clang loop unroll(full)
-    for (int i = 0; i < MB; ++i) {
-      // (96-row tiles may end past np: those blocks take the last one's rows)
-      const float* ra = ga + int64_t(min(R0 + 32 * i, np - 32)) * np;
-      const float* rb = gb + int64_t(min(C0 + 32 * i, np - 32)) * np;
-#pragma clang loop unroll(full)
-      for (int u = 0; u < 2; ++u) {
-        dma_chunk(own, ra + u * 16 * int64_t(np), m0s + i * 2048 + u * 1024);
-        dma_chunk(own, rb + u * 16 * int64_t(np), m0s + (MB + i) * 2048 + u * 1024);
-      }
-    }
+  struct Source {
+    const float *a, *b;
   };
-  if (qn > 0) {
+  auto source = [&](int q) {   // step q
+    int x = s0 + q;
+    const int sg = (NSEG > 1 && x >= ks) + (NSEG > 2 && x >= 2 * ks) + (NSEG > 2 && x >= 3 * ks);
+    x -= sg * ks;
+    return Source{(sg == 0 ? p.a[0] : sg == 1 ? p.a[1] : sg == 2 ? p.a[2] : p.a[3]) + x * 16,
+                  (sg == 0 ? p.b[0] : sg == 1 ? p.b[1] : sg == 2 ? p.b[2] : p.b[3]) + x * 16};
+  };
+  // Copy c of step q into its slot: half u of block i of an operand (96-row tiles
+  // may end past np: those blocks take the last one's rows).
+  auto copy = [&](const Source& g, int q, int c) {
+    const int i = c / 4, u = c / 2 % 2, isb = c % 2;
+    const float* rows = (isb ? g.b : g.a) +
+                        (int64_t(min((isb ? C0 : R0) + 32 * i, np - 32)) + u * 16) * np;
+    dma_chunk(own, rows, ring0 + (q & (NS - 1)) * kSlot + (isb * MB + i) * 2048 + u * 1024);
+  };
 #pragma clang loop unroll(full)
-    for (int i = 0; i < NS; ++i) copy(min(i, qn - 1), i);
-  }
+  for (int i = 0; i < NS; ++i)
+    if (i < qn) {
+      const Source g = source(i);
+#pragma clang loop unroll(full)
+      for (int c = 0; c < kCopies; ++c) copy(g, i, c);
+    }
 
   const LayerCoef cf = decide_layer_wave(p.dec);
   float alpha = p.epi.alpha, beta = p.epi.beta, gamma = p.epi.gamma;
@@ -847,13 +802,13 @@ void k_wave_f32(WaveF32Args p) {
     beta = uniform(beta);
     gamma = uniform(gamma);
   }
-  f32x16 acc[MB][MB], crs[MB][MB];
+  f32x16 acc[MB][MB], sum[MB][MB];
 #pragma clang loop unroll(full)
   for (int mi = 0; mi < MB; ++mi)
 #pragma clang loop unroll(full)
     for (int ni = 0; ni < MB; ++ni)
 #pragma clang loop unroll(full)
-      for (int q = 0; q < 16; ++q) acc[mi][ni][q] = crs[mi][ni][q] = 0.0f;
+      for (int q = 0; q < 16; ++q) sum[mi][ni][q] = 0.0f;
   // this lane's two 16-byte pieces of its row (values 8 h .. 8 h + 7) in a block
   const int r = lane & 31, h2 = (lane >> 5) * 2;
   const int f0 = r * 64 + ((h2 ^ ((r >> 1) & 3)) * 16), f1 = r * 64 + (((h2 + 1) ^ ((r >> 1) & 3)) * 16);
@@ -861,151 +816,74 @@ void k_wave_f32(WaveF32Args p) {
   wait_vmem_all();   // the decision's loads, and with them the first copies
   if (cf.sign == 0) return;
 
-  // The reads of slot q are done: it takes step q + NS (at the end the last step
-  // again, which is not read, so that the count of copies in flight stays).
-  // After it step q + 1 has arrived.
-  auto refill = [&](int q) {
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    copy(min(q + NS, qn - 1), q);
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * kCopies) : "memory");
+  struct Frag {   // half a step: one of the two pieces of every block
+    f32x4 a[MB], b[MB];
   };
-  // The steps with diagonal entries, on the FP32 cores: a BF16 MFMA adds its
-  // products in groups of eight and cuts each off about 2^-25 below the largest
-  // of its group, towards zero.  Beside the product of a diagonal entry the
-  // squares on the diagonal of S S^T would all lose by that, a bias that the
-  // trace collects: over an FP32 solve of n = 256 the recorded traces were off
-  // by up to 1.2e-4; so it is 1.3e-5 (3.0e-5 with FP32 products throughout).  Lane (r, h) feeds value 8 h + e of
-  // row r to product e.
-  for (int q = 0; q < qd; ++q) {
-    const char* sl = ring + (q & (NS - 1)) * kSlot;
-    f32x4 xa[MB][2], xb[MB][2];
+  auto read = [&](Frag& f, int q, int off) {
+    const char* sl = ring + (q & (NS - 1)) * kSlot + off;
 #pragma clang loop unroll(full)
     for (int i = 0; i < MB; ++i) {
-      xa[i][0] = *reinterpret_cast<const f32x4*>(sl + i * 2048 + f0);
-      xa[i][1] = *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1);
-      xb[i][0] = *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0);
-      xb[i][1] = *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1);
+      f.a[i] = *reinterpret_cast<const f32x4*>(sl + i * 2048);
+      f.b[i] = *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048);
     }
     __builtin_amdgcn_sched_barrier(0);
-    refill(q);
-    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Four products of every pair of blocks, half a step; first: of a new sum.
+  auto products = [&](const Frag& f, auto first) {
 #pragma clang loop unroll(full)
-    for (int e = 0; e < 8; ++e)
+    for (int e = 0; e < 4; ++e)
 #pragma clang loop unroll(full)
       for (int mi = 0; mi < MB; ++mi)
 #pragma clang loop unroll(full)
-        for (int ni = 0; ni < MB; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[mi][e / 4][e % 4], xb[ni][e / 4][e % 4],
-                                                             acc[mi][ni], 0, 0, 0);
-  }
-  constexpr int ta[6] = {0, 0, 1, 1, 0, 2}, tb[6] = {0, 1, 0, 1, 2, 0};   // hh hm mh mm hl lh
-  if constexpr (MB < 3) {
-    struct Planes {
-      u32x4 a[3][MB], b[3][MB];
-    };
-    auto convert = [&](Planes& f, int q) {   // step q from its slot
-      const char* sl = ring + (q & (NS - 1)) * kSlot;
+        for (int ni = 0; ni < MB; ++ni) {
+          if (decltype(first)::value && e == 0) {
 #pragma clang loop unroll(full)
-      for (int i = 0; i < MB; ++i) {
-        split3(*reinterpret_cast<const f32x4*>(sl + i * 2048 + f0),
-               *reinterpret_cast<const f32x4*>(sl + i * 2048 + f1), f.a[0][i], f.a[1][i], f.a[2][i]);
-        split3(*reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f0),
-               *reinterpret_cast<const f32x4*>(sl + (MB + i) * 2048 + f1), f.b[0][i], f.b[1][i],
-               f.b[2][i]);
-      }
-    };
-    // Step q from cur while step q + 1 is split into nxt.
-    auto step = [&](const Planes& cur, Planes& nxt, int q) {
-      refill(q);
-      __builtin_amdgcn_sched_barrier(0);
-      convert(nxt, q + 1);
+            for (int k = 0; k < 16; ++k) acc[mi][ni][k] = 0.0f;
+          }
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(f.a[mi][e], f.b[ni][e], acc[mi][ni], 0, 0, 0);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  Frag x, y;
+  read(x, 0, f0);
+  auto step = [&](int q, auto first) {
+    read(y, q, f1);
+    products(x, first);
+    // The reads of step q are done: its slot takes step q + NS.  Step q + 1 has
+    // arrived once no more than the copies after it are outstanding (at the end a
+    // slot that no step fills any more is read, and not used).
+    if (q + NS < qn) {
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      const Source g = source(q + NS);
 #pragma clang loop unroll(full)
-      for (int k = 0; k < 6; ++k)
-#pragma clang loop unroll(full)
-        for (int mi = 0; mi < MB; ++mi)
-#pragma clang loop unroll(full)
-          for (int ni = 0; ni < MB; ++ni)
-            mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], cur.a[ta[k]][mi],
-                                   cur.b[tb[k]][ni]);
-      // the reads first, then the conversions spread over the MFMAs
-      __builtin_amdgcn_sched_group_barrier(0x100, 4 * MB, 0);
-#pragma clang loop unroll(full)
-      for (int k = 0; k < 6 * MB * MB; ++k) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, MB == 1 ? 16 : 8, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    Planes f0s, f1s;
-    if (qn > qd) convert(f0s, qd);
-    for (int q = qd; q < qn; q += 2) {
-      step(f0s, f1s, q);
-      step(f1s, f0s, q + 1);
+      for (int c = 0; c < kCopies; ++c) copy(g, q, c);
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 1) * kCopies) : "memory");
+    } else {
+      wait_vmem_all();
     }
-  } else {
-    // One wave per SIMD: a row of three blocks is multiplied while the next A
-    // block is split, the last row while the first A block and the B blocks of
-    // step q + 1 are (two steps' planes of both operands would not fit).
-    struct Tri {
-      u32x4 v[3];
-    };
-    auto split = [&](Tri& x, int q, int block) {   // A blocks, then B blocks
-      const char* sl = ring + (q & (NS - 1)) * kSlot + block * 2048;
-      split3(*reinterpret_cast<const f32x4*>(sl + f0), *reinterpret_cast<const f32x4*>(sl + f1), x.v[0],
-             x.v[1], x.v[2]);
-    };
-    auto row = [&](const Tri& a, const Tri (&b)[MB], int mi, auto last) {
-#pragma clang loop unroll(full)
-      for (int k = 0; k < 6; ++k)
-#pragma clang loop unroll(full)
-        for (int ni = 0; ni < MB; ++ni)
-          mfma_32x32x16<kBF16X3>(k == 0 ? acc[mi][ni] : crs[mi][ni], a.v[ta[k]], b[ni].v[tb[k]]);
-      constexpr int kBlocks = decltype(last)::value ? 1 + MB : 1;
-      __builtin_amdgcn_sched_group_barrier(0x100, 2 * kBlocks, 0);
-#pragma clang loop unroll(full)
-      for (int k = 0; k < 6 * MB; ++k) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, (40 * kBlocks + 6 * MB - 1) / (6 * MB), 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    auto step = [&](Tri& a, Tri& a2, Tri (&b)[MB], Tri (&nb)[MB], int q) {   // row 0 in a
-      split(a2, q, 1);
-      row(a, b, 0, std::false_type());
-      split(a, q, 2);
-      row(a2, b, 1, std::false_type());
-      refill(q);
-      __builtin_amdgcn_sched_barrier(0);
-      split(a2, q + 1, 0);
-#pragma clang loop unroll(full)
-      for (int i = 0; i < MB; ++i) split(nb[i], q + 1, MB + i);
-      row(a, b, 2, std::true_type());
-    };
-    Tri a0, a1, b0[MB], b1[MB];
-    if (qn > qd) {
-      split(a0, qd, 0);
-#pragma clang loop unroll(full)
-      for (int i = 0; i < MB; ++i) split(b0[i], qd, MB + i);
-    }
+    read(x, q + 1, f0);
+    products(y, std::false_type());
+  };
 #pragma clang loop unroll(disable)
-    for (int q = qd; q < qn; q += 2) {
-      step(a0, a1, b0, b1, q);
-      step(a1, a0, b1, b0, q + 1);
-    }
+  for (int q = 0; q < qn;) {
+    const int qe = min(q + kF32Cut<MB>, qn);
+    step(q, std::true_type());
+#pragma clang loop unroll(disable)
+    while (++q < qe) step(q, std::false_type());
+#pragma clang loop unroll(full)
+    for (int mi = 0; mi < MB; ++mi)
+#pragma clang loop unroll(full)
+      for (int ni = 0; ni < MB; ++ni)
+#pragma clang loop unroll(full)
+        for (int k = 0; k < 16; ++k) sum[mi][ni][k] += acc[mi][ni][k];
   }
-#pragma clang loop unroll(full)
-  for (int mi = 0; mi < MB; ++mi)
-#pragma clang loop unroll(full)
-    for (int ni = 0; ni < MB; ++ni)
-#pragma clang loop unroll(full)
-      for (int q = 0; q < 16; ++q) acc[mi][ni][q] = add_cross(acc[mi][ni][q], crs[mi][ni][q]);
   if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);   // no registers for C before
   f32x4 cs[MB][Sh::groups(NW)];
 #pragma clang loop unroll(full)
   for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
   wait_vmem_all();
   __syncthreads();   // the rings are free
-  wave_epilogue<kF32, MB>(acc, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, NW, lane, lds,
+  wave_epilogue<kF32, MB>(sum, cs, p.epi, alpha * p.epi.oscale, beta, gamma, R0, C0, w, NW, lane, lds,
                           red, tile);
 }
 
