@@ -631,24 +631,24 @@ sp2_status launch_wave_f32(const WS& w, const F32Args& a, hipStream_t st) {
   return SP2_OK;
 }
 
-// Launch an FP32 product sum_s A_s B_s^T (nseg <= 4; row-major operands,
-// leading dimension np), then the strip kernel for its split-K tail tiles.
-sp2_status launch_f32(const WS& w, int nseg, const float* const* A, const float* const* B,
+// Launch an FP32 product sum_s A_s B_s^T (1, 2 or 4 row-major operands of
+// leading dimension np each; k_wave_f32 reads as many as its template says),
+// then the strip kernel for its split-K tail tiles.
+template <int NSEG>
+sp2_status launch_f32(const WS& w, const float* const (&A)[NSEG], const float* const (&B)[NSEG],
                       const Epi& epi, const Decide& dec, hipStream_t st) {
+  static_assert(NSEG == 1 || NSEG == 2 || NSEG == 4, "segments of an FP32 product");
   F32Args a;
   memset(&a, 0, sizeof(a));
-  for (int s = 0; s < nseg; ++s) {
+  for (int s = 0; s < NSEG; ++s) {
     a.a[s] = A[s];
     a.b[s] = B[s];
   }
-  a.nseg = nseg;
+  a.nseg = NSEG;
   a.epi = epi;
   a.dec = dec;
-  if (wave_rows_f32(w.L)) {
-    if (nseg == 1) return launch_wave_f32<1>(w, a, st);
-    return nseg == 2 ? launch_wave_f32<2>(w, a, st) : launch_wave_f32<4>(w, a, st);
-  }
-  a.dc = f32_decomp(w, nseg);
+  if (wave_rows_f32(w.L)) return launch_wave_f32<NSEG>(w, a, st);
+  a.dc = f32_decomp(w, NSEG);
   const int ntail = a.dc.ntiles - a.dc.nfull;
   k_sym_f32<<<a.dc.nfull + ntail * a.dc.nsplit, 256, 0, st>>>(a);
   LAUNCH_TRY();
@@ -708,7 +708,7 @@ sp2_status launch_layer(const WS& w, int precision, int n, int mode, const float
   e.n_diag = static_cast<int>(w.L.n);   // the c I term of a shifted layer: real rows only
   if (precision == SP2_FP32) {
     const float* A[1] = {src};
-    return launch_f32(w, 1, A, A, e, d, st);
+    return launch_f32(w, A, A, e, d, st);
   }
   e.split_out = split_code_of(precision);
   e.hi_out = w.hi(pair_out);
@@ -832,9 +832,9 @@ sp2_status refine(const WS& w, int precision, int refine_mode, int n_iter, const
   sp2_status s;
   if (refine_mode == SP2_REFINE_FP32) {
     const float* A[1] = {S};
-    if ((s = launch_f32(w, 1, A, A, e1, d0, st))) return s;
+    if ((s = launch_f32(w, A, A, e1, d0, st))) return s;
     const float* B[1] = {S2};
-    if ((s = launch_f32(w, 1, A, B, e2, d0, st))) return s;
+    if ((s = launch_f32(w, A, B, e2, d0, st))) return s;
     return SP2_OK;
   }
   // FP16X3 split refinement with S's planes centred (c = kPlaneCentre, pair
@@ -1488,7 +1488,7 @@ sp2_status sp2_layer(const float* X, int64_t n, int64_t ld, int32_t precision, i
   sp2_status s;
   if (precision == SP2_FP32) {
     const float* A[1] = {Xp};
-    s = launch_f32(w, 1, A, A, e, d0, st);
+    s = launch_f32(w, A, A, e, d0, st);
   } else {
     e.beta += 2.0f * kPlaneCentre * e.alpha;
     e.gamma = -kPlaneCentre * kPlaneCentre * e.alpha;
@@ -1577,7 +1577,7 @@ sp2_status sym_pair(const WS& w, const float* X, const float* Y, const float* C,
   e.out = out;
   e.alpha = alpha;
   e.beta = beta;
-  return launch_f32(w, 2, A, B, e, make_decide(w, mode, layer), st);
+  return launch_f32(w, A, B, e, make_decide(w, mode, layer), st);
 }
 
 // Split derivatives (SP2_FLAG_SPLIT_DERIVATIVES with BF16X3 layers): the
@@ -1627,7 +1627,7 @@ sp2_status refine_derivative(const WS& w, const float* S, const float* D, float*
     const float* A[1] = {S};
     Epi e = make_epi(w.L);
     e.out = S2;
-    if ((s = launch_f32(w, 1, A, A, e, make_decide(w, 0, 0), st))) return s;
+    if ((s = launch_f32(w, A, A, e, make_decide(w, 0, 0), st))) return s;
   }
   const float* A[4] = {S, M, S2, D};
   const float* B[4] = {M, S, D, S2};
@@ -1639,7 +1639,7 @@ sp2_status refine_derivative(const WS& w, const float* S, const float* D, float*
   e.vec_ok = vec_ok;
   e.alpha = -1.0f;
   e.beta = 3.0f;
-  return launch_f32(w, 4, A, B, e, make_decide(w, 0, 0), st);
+  return launch_f32(w, A, B, e, make_decide(w, 0, 0), st);
 }
 
 // The same map in BF16X3 products (split derivatives): S given by its

@@ -6,7 +6,7 @@ import shutil
 
 import pytest
 
-from paper_2107_02737_amd.build import hipcc, kernel_resources
+from paper_2107_02737_amd.build import compile_command, hipcc, kernel_resources
 
 
 @pytest.fixture(scope="module")
@@ -50,6 +50,27 @@ def test_layer_kernels_fit_their_occupancy(resources):
         if "k_sym" in name:
             assert r["vgpr_count"] <= 512, name
             assert r["group_segment_fixed_size"] <= 160 * 1024, name
+
+
+@pytest.mark.parametrize("segments", [1, 2, 3, 4])
+def test_segments_of_an_fp32_product(tmp_path, segments):
+    """A launch passes as many operands as its kernel reads: a sum of three does
+    not compile (the four-segment kernel would read a null operand)."""
+    import subprocess
+    src = tmp_path / "segments.hip"
+    src.write_text(f"""
+#include "sp2_capi.hip"
+sp2_status call(const WS& w, const float* x, const Epi& e, const Decide& d, hipStream_t st) {{
+  const float* A[{segments}] = {{{", ".join(["x"] * segments)}}};
+  return launch_f32(w, A, A, e, d, st);
+}}
+""")
+    cmd = [c for c in compile_command(str(tmp_path / "out"), [str(src)]) if c != "-shared"]
+    res = subprocess.run(cmd[:-2] + ["--offload-host-only", "-fsyntax-only"], capture_output=True,
+                         text=True)
+    assert (res.returncode == 0) == (segments != 3), res.stderr
+    if segments == 3:
+        assert "segments of an FP32 product" in res.stderr
 
 
 def test_hipcc_on_path_or_rocm():
