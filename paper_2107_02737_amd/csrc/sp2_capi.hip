@@ -987,12 +987,16 @@ sp2_status noalloc_scratch(void** out) {
 }
 
 // Wait until the mail word of solve `token` shows the stop or a layer of at least
-// `layer`; the word's state (0: not stopped) goes to *state.  The stream is
-// queried now and then: a fault on it ends the wait, and on a drained stream
-// whose word is another's (a call that failed before left launches behind) the
-// control block is read instead.
+// `layer`; the word's state (0: not stopped) goes to *state.  The thread spins, as
+// it does in the runtime's own waits.  The stream is queried after about 20 ms (two
+// layers of n = 16384) and then whenever the wait has doubled: a fault on it ends the
+// wait, and on a drained stream whose word is another's (a call that failed before
+// left launches behind) the control block is read instead.  A query, however seldom,
+// keeps a thread of the runtime busy for a while: every 0.15 ms, or three in each
+// layer of n = 16384, for 15% of the solve (2% without, as with event waits).
 sp2_status await_layer(const WS& w, HostMirror* hm, uint32_t token, int layer, hipStream_t st,
                        uint64_t* state) {
+  constexpr uint32_t kFirstQuery = 1u << 19;   // turns of some 40 ns
   *state = 0;
   for (uint32_t spin = 1;; ++spin) {
     const uint64_t m = __atomic_load_n(&hm->mail, __ATOMIC_ACQUIRE);
@@ -1003,7 +1007,8 @@ sp2_status await_layer(const WS& w, HostMirror* hm, uint32_t token, int layer, h
       }
       if (static_cast<int>(m & 0xffff) > layer) return SP2_OK;
     }
-    if (spin % 4096 == 0) {
+    if (spin % 4096 == 0) std::this_thread::yield();
+    if (spin >= kFirstQuery && (spin & (spin - 1)) == 0) {
       const hipError_t e = hipStreamQuery(st);
       if (e == hipSuccess && __atomic_load_n(&hm->mail, __ATOMIC_ACQUIRE) == m) {
         if (sp2_status s = read_back(w, hm, false, st)) return s;
@@ -1017,7 +1022,6 @@ sp2_status await_layer(const WS& w, HostMirror* hm, uint32_t token, int layer, h
       if (e != hipSuccess && e != hipErrorNotReady)
         return fail(SP2_ERR_DEVICE, "poll: %s", hipGetErrorString(e));
       (void)hipGetLastError();   // not-ready is no error of the next launch
-      std::this_thread::yield();
     }
     __builtin_ia32_pause();
   }
