@@ -52,6 +52,27 @@ def test_layer_kernels_fit_their_occupancy(resources):
             assert r["group_segment_fixed_size"] <= 160 * 1024, name
 
 
+def test_kernels_of_smaller_orders(resources):
+    """Every tile size of every kind is there, without spills in the loop, within the
+    registers and the LDS of its occupancy."""
+    names = " ".join(resources)
+    for kind in range(3):
+        for rows in (1, 2, 3):
+            assert f"k_sym_waveILi{kind}ELi{rows}ELi1EE" in names
+        assert f"k_sym_midILi{kind}ELi1EE" in names
+    for rows in (1, 2, 3):
+        assert f"k_sym_waveILi0ELi{rows}ELi2EE" in names
+        for segments in (1, 2, 4):
+            assert f"k_wave_f32ILi{rows}ELi{segments}EE" in names
+    assert "k_sym_midILi0ELi2EE" in names
+    for name, r in resources.items():
+        if "k_wave_f32" in name:
+            assert r["hot_loop_scratch"] == 0, name
+            # eight waves, two per SIMD; four of the 96-row tiles
+            assert r["vgpr_count"] <= (512 if "ILi3E" in name else 256), name
+            assert r["group_segment_fixed_size"] <= 160 * 1024, name
+
+
 @pytest.mark.parametrize("segments", [1, 2, 3, 4])
 def test_segments_of_an_fp32_product(tmp_path, segments):
     """A launch passes as many operands as its kernel reads: a sum of three does

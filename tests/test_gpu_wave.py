@@ -211,3 +211,11 @@ def test_fp32_96_row_tiles(pk, n):
     test_fp32_layer_at_tile_edges(pk, n)
     if n == 2047:
         test_fp32_pair_products(pk, n)
+
+
+@pytest.mark.parametrize("n", [1791, 1792])
+def test_last_orders_of_64_row_tiles(pk, n):
+    """Both kinds of 64-row tiles, split and FP32, serve n <= 1792."""
+    test_layer_at_tile_edges(pk, n)
+    test_traces_are_those_of_the_iterate(pk, n)
+    test_fp32_layer_at_tile_edges(pk, n)
