@@ -413,7 +413,8 @@ Decomp split_decomp_of(const WS& w, int precision) {
   return split_decomp<kFP16X3>(w);
 }
 
-// K pieces of a split product on k_sym_wave, those of the 256 x 256 kernel.
+// K pieces of a split product on k_sym_wave: those of the 256 x 256 kernel, at most
+// as many as a work-group has waves (fewer only with two segments, n = 769 to 1280).
 int wave_pieces(const Layout& L, int nseg) {
   WS none{};
   const Decomp d = plan_decomp(none, L.nb_split, device_cus(), static_cast<int>(L.np / 32) * nseg,

@@ -8,7 +8,9 @@
 // a time, where the epilogue finishes them: one launch per product, no partial
 // accumulators in memory.  The pieces are those of the split-K plan of the
 // 256 x 256 kernel and are summed in their order, so a product is the same bit
-// for bit as there.  At n = 402 (32-row tiles, 4 waves) a layer takes 8.6 us
+// for bit as there, but for two-segment products of n = 769 to 1280, whose plan
+// has 16 or 17 pieces and a work-group at most 12 waves (error of a BF16X3
+// derivative of those orders: 1.00 times that of the plan).  At n = 402 (32-row tiles, 4 waves) a layer takes 8.6 us
 // against 25.8 us in the 256 x 256 kernel and its split-K strip kernel, at
 // n = 1026 17.7 against 35.6 us, at n = 2046 (96-row tiles, 7 waves) 42 against
 // 58.6 us.  At 402 and 1026 that is a decision head of 2 us, a K loop of 0.3 to
