@@ -796,14 +796,6 @@ void k_wave_f32(WaveF32Args p) {
     beta = cf.b;
     gamma = cf.c;
   }
-  if constexpr (MB > 2) {   // uniform, and no vector register is left for them
-    auto uniform = [](float x) {
-      return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
-    };
-    alpha = uniform(alpha);
-    beta = uniform(beta);
-    gamma = uniform(gamma);
-  }
   f32x16 acc[MB][MB], sum[MB][MB];
 #pragma clang loop unroll(full)
   for (int mi = 0; mi < MB; ++mi)
@@ -879,7 +871,6 @@ void k_wave_f32(WaveF32Args p) {
 #pragma clang loop unroll(full)
         for (int k = 0; k < 16; ++k) sum[mi][ni][k] += acc[mi][ni][k];
   }
-  if constexpr (MB > 2) __builtin_amdgcn_sched_barrier(0);   // no registers for C before
   f32x4 cs[MB][Sh::groups(NW)];
 #pragma clang loop unroll(full)
   for (int mi = 0; mi < MB; ++mi) wave_load_c<MB>(cs[mi], p.epi, R0, C0, mi);
